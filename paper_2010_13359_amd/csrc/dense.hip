@@ -97,48 +97,12 @@ __global__ __launch_bounds__(kBlock) void k_segment_partials(const float *__rest
     }
 }
 
-// Combine the partials of each (worker, segment) in piece order, or take the
-// caller's scales, and derive the per-segment constants (SegConst): SIGN the
-// scale; QSGD, MBIT fl(s/(u sigma)) and fl(u sigma/s), negated when u = 2^64
-// (sigma < 2^-64), zeros for sigma = 0 or not finite.  Quotients of two
-// binary32 values computed in binary64 and rounded to binary32 equal the
-// correctly rounded binary32 quotient (53 >= 2*24 + 2).
-__global__ __launch_bounds__(kBlock) void k_finalize(int kind, int norm, int levels, const double *__restrict__ partial,
-                                                     const float *__restrict__ pmax, int32_t n_pieces,
-                                                     const int32_t *__restrict__ seg_piece,
-                                                     const int64_t *__restrict__ off, int32_t M, int32_t n_seg,
-                                                     const float *__restrict__ scales_in, float *__restrict__ scale_out,
-                                                     SegConst *__restrict__ consts) {
-    // One wave per (worker, segment): lane l adds the segment's pieces
-    // l, l+64, ... in order, then a fixed butterfly combines the lanes.
-    const int64_t tid = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    if (tid >= static_cast<int64_t>(M) * n_seg) return;
-    const int m = static_cast<int>(tid / n_seg);
-    const int j = static_cast<int>(tid % n_seg);
-    float sc;
-    if (scales_in) {
-        sc = scales_in[tid];
-    } else if (norm == DQGAN_LINF) {
-        float mx = 0.0f;
-        for (int p = seg_piece[j] + lane; p < seg_piece[j + 1]; p += 64)
-            mx = fmaxf(mx, pmax[static_cast<int64_t>(m) * n_pieces + p]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-        sc = mx;
-    } else {
-        double s = 0.0;
-        for (int p = seg_piece[j] + lane; p < seg_piece[j + 1]; p += 64)
-            s += partial[static_cast<int64_t>(m) * n_pieces + p];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-        if (norm == DQGAN_L1)
-            sc = static_cast<float>(s / static_cast<double>(off[j + 1] - off[j]));
-        else
-            sc = static_cast<float>(sqrt(s));
-    }
-    if (lane != 0) return;
-    if (scale_out) scale_out[tid] = sc;
+// The per-segment constants (SegConst) of a scale: SIGN the scale; QSGD, MBIT
+// fl(s/(u sigma)) and fl(u sigma/s), negated when u = 2^64 (sigma < 2^-64),
+// zeros for sigma = 0 or not finite.  Quotients of two binary32 values
+// computed in binary64 and rounded to binary32 equal the correctly rounded
+// binary32 quotient (53 >= 2*24 + 2).
+__device__ __forceinline__ SegConst seg_const(int kind, int levels, float sc) {
     SegConst c{sc, 0.0f};
     if (kind == kQsgd || kind == kMbit) {
         c.a = 0.0f;
@@ -154,7 +118,49 @@ __global__ __launch_bounds__(kBlock) void k_finalize(int kind, int norm, int lev
             }
         }
     }
-    consts[tid] = c;
+    return c;
+}
+
+// The scale of one (worker, segment) from its pieces' partials, by a whole
+// wave: lane l adds the segment's pieces p0 + l, p0 + l + 64, ... in order,
+// then a fixed butterfly combines the lanes (every lane gets the result).
+// `partial` and `pmax` point at the worker's row; n = the segment's elements.
+__device__ __forceinline__ float segment_scale(int norm, const double *__restrict__ partial,
+                                               const float *__restrict__ pmax, int p0, int p1, int64_t n) {
+    const int lane = threadIdx.x & 63;
+    if (norm == DQGAN_LINF) {
+        float mx = 0.0f;
+        for (int p = p0 + lane; p < p1; p += 64) mx = fmaxf(mx, pmax[p]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        return mx;
+    }
+    double s = 0.0;
+    for (int p = p0 + lane; p < p1; p += 64) s += partial[p];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    return norm == DQGAN_L1 ? static_cast<float>(s / static_cast<double>(n)) : static_cast<float>(sqrt(s));
+}
+
+// The scale and constants of every (worker, segment), one wave each, from
+// the partials or from the caller's scales.
+__global__ __launch_bounds__(kBlock) void k_finalize(int kind, int norm, int levels, const double *__restrict__ partial,
+                                                     const float *__restrict__ pmax, int32_t n_pieces,
+                                                     const int32_t *__restrict__ seg_piece,
+                                                     const int64_t *__restrict__ off, int32_t M, int32_t n_seg,
+                                                     const float *__restrict__ scales_in, float *__restrict__ scale_out,
+                                                     SegConst *__restrict__ consts) {
+    const int64_t tid = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) >> 6;
+    if (tid >= static_cast<int64_t>(M) * n_seg) return;
+    const int m = static_cast<int>(tid / n_seg);
+    const int j = static_cast<int>(tid % n_seg);
+    const int64_t row = static_cast<int64_t>(m) * n_pieces;
+    const float sc = scales_in ? scales_in[tid]
+                               : segment_scale(norm, partial + row, pmax + row, seg_piece[j], seg_piece[j + 1],
+                                               off[j + 1] - off[j]);
+    if ((threadIdx.x & 63) != 0) return;
+    if (scale_out) scale_out[tid] = sc;
+    consts[tid] = seg_const(kind, levels, sc);
 }
 
 // r = fl(|p| s / sigma) of equation (qsgd) from the constant a of SegConst
@@ -303,6 +309,13 @@ __device__ __forceinline__ void lookup_segments(const int64_t *__restrict__ off,
         j = seg_from(off, j, i < last ? i : last);
         js[c] = j;
     }
+}
+
+// The segment of element min(i, d - 1), for an i that is the same for the
+// whole wave: scalar loads, off the vector memory queue.
+__device__ __forceinline__ int uniform_segment(const int64_t *__restrict__ off, const int32_t *__restrict__ tile_seg,
+                                               int64_t i, int64_t d) {
+    return seg_from(off, tile_seg[i >> 10], i < d ? i : d - 1);
 }
 
 // Message stores for one quad of one row (every lane of the wave active);
@@ -528,20 +541,32 @@ __global__ __launch_bounds__(64 * NG) void k_fused_split(const float *__restrict
     const int last_g = (M - 1) / R;  // the wave that finishes the sum
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 64 + lane;
     const int64_t i0 = 4 * q;
-    int js[4];
-    lookup_segments(off, tile_seg, i0, a.d, js);
-    // One segment for the whole wave (the common case): its constants are
-    // fetched with one scalar load per row.
-    const int j_first = __builtin_amdgcn_readfirstlane(js[0]);
-    const bool one_seg = __ballot(js[0] != j_first || js[3] != j_first) == 0;
+    // One row per wave (every wave that is launched owns one): its loads go
+    // out before anything is looked up.
+    f32x4 g_first, e_first;
+    if constexpr (R == 1) {
+        const int64_t rb0 = static_cast<int64_t>(g) * a.ld;
+        g_first = ld_stream(G + rb0 + i0);
+        e_first = ld_stream(E + rb0 + i0);
+    }
+    // The workgroup's first segment, by scalar loads, and whether it holds
+    // all of the workgroup's columns (the common case): then a row's
+    // constants are one scalar load, and no lane looks up its elements'
+    // segments (a chain of dependent vector loads before the first row).
+    const int64_t c0 = static_cast<int64_t>(blockIdx.x) * 256;
+    const int64_t c1 = c0 + 256 < a.d ? c0 + 256 : a.d;
+    const int j_first = KIND == kTopk || KIND == kIdentity ? 0 : uniform_segment(off, tile_seg, c0, a.d);
+    const bool one_seg = KIND == kTopk || KIND == kIdentity || off[j_first + 1] >= c1;
+    int js[4] = {j_first, j_first, j_first, j_first};
+    if (!one_seg) lookup_segments(off, tile_seg, i0, a.d, js);
     f32x4 ph[R], xs[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int m = g * R + r;
         if (m < M) {
             const int64_t rb = static_cast<int64_t>(m) * a.ld;
-            const f32x4 gv = ld_stream(G + rb + i0);
-            const f32x4 ev = ld_stream(E + rb + i0);
+            const f32x4 gv = R == 1 ? g_first : ld_stream(G + rb + i0);
+            const f32x4 ev = R == 1 ? e_first : ld_stream(E + rb + i0);
             const SegConst *crow = consts + static_cast<int64_t>(m) * a.n_seg;
             QuadCodes cq;
             if constexpr (KIND == kTopk) {
@@ -948,19 +973,35 @@ hipError_t fused_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
     return hipGetLastError();
 }
 
+// LDS per workgroup that leaves room for 24 waves per CU with two rows per
+// wave and for 16 with four (160 KB per CU).  HBM serves the pass's mix of
+// reads and writes faster with fewer rows in flight: 16 workers x 6.3M 8-bit
+// codes, whole step 464.5 us at 32 waves, 453.0 at 24, 469.2 at 16; 32 workers
+// x 2^25, s = 15: 4662 us at 24 waves (all that its registers allow), 4609
+// at 16, 6337 at 8; 16 workers x 10^8 top-k 7210 us at 32, 7092 at 24, 7661
+// at 16.  Steps that the Infinity Cache holds are not capped.
+constexpr unsigned cap_lds(int R, int NG) {
+    return NG != 8 ? 0u : R == 2 ? 52000u : R == 4 ? 79000u : 0u;
+}
+
 template <int KIND, int LB, int R, int NG>
 hipError_t split_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G, float *E, float *W, float *WX,
                         const dqgan_wire &w, float *Qhat, hipStream_t st) {
     if (P.desc.M > R * NG) return hipErrorInvalidValue;  // every worker must belong to a wave
     const TopkArgs ta = topk_args(P, w);
-    const dim3 grid(static_cast<unsigned>(P.n_tiles * 4)), block(64 * NG);
+    // only the waves that own a row
+    const dim3 grid(static_cast<unsigned>(P.n_tiles * 4)), block(64 * static_cast<unsigned>((P.desc.M + R - 1) / R));
+    // Unused LDS that caps the workgroups per CU of a step that streams from
+    // HBM (see fused_by_m).
+    const double bytes = 16.0 * P.desc.M * static_cast<double>(P.desc.ld);
+    const unsigned cap = bytes > kInfinityCacheBytes ? cap_lds(R, NG) : 0u;
     // Only 8-bit planes have a second store kind (store_fields32).
     constexpr bool kTwoKinds = (KIND == kQsgd || KIND == kMbit) && LB == 8;
     if (kTwoKinds && a.stream_msg)
-        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, kTwoKinds>), grid, block, 0, st, G, E, W, WX, Qhat, w.sign,
+        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, kTwoKinds>), grid, block, cap, st, G, E, W, WX, Qhat, w.sign,
                            w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a, inv_m(P.desc.M), ta);
     else
-        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, false>), grid, block, 0, st, G, E, W, WX, Qhat, w.sign,
+        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, false>), grid, block, cap, st, G, E, W, WX, Qhat, w.sign,
                            w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a, inv_m(P.desc.M), ta);
     return hipGetLastError();
 }
