@@ -36,10 +36,9 @@
  *    nothing.  A failed launch returns DQGAN_EHIP; faults of enqueued work
  *    surface at the caller's next synchronization.  No call aborts the
  *    process.  Only dqgan_plan_create and dqgan_plan_destroy allocate or free
- *    device memory.  The per-iteration calls enqueue kernels only (plus, in
- *    dqgan_pack, one device-to-device copy of the scales): no memset, no host
- *    synchronization, so a caller may capture them in a HIP graph and replay
- *    it.
+ *    device memory.  The per-iteration calls enqueue kernels only: no copy, no
+ *    memset, no host synchronization, so a caller may capture them in a HIP
+ *    graph and replay it.
  *  - A plan is bound to the device that was current at its creation; calls
  *    must be made with that device current.  A plan is not thread-safe, and
  *    two calls on one plan must not run concurrently on different streams

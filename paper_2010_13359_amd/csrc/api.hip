@@ -167,6 +167,10 @@ dqgan_status dqgan_plan_create(const dqgan_desc *desc, dqgan_plan *out) {
             const int64_t i = tl * 1024 < d ? tl * 1024 : d - 1;
             while (P->offsets[j + 1] <= i) ++j;
             tile_seg[static_cast<size_t>(tl)] = j;
+            const int64_t end = tl * 1024 + 1024 < d ? tl * 1024 + 1024 : d;
+            int32_t n = 1;
+            while (P->offsets[j + n] < end) ++n;
+            if (n > P->max_tile_segs) P->max_tile_segs = n;
         }
     }
     const int64_t piece = static_cast<int64_t>(desc->M) * (d / dq::kPieceElems) >= dq::kPieceBlocksForLong
@@ -263,12 +267,7 @@ dqgan_status dqgan_pack(dqgan_plan P, const uint16_t *codes, const float *scales
     DQ_TRY(check_wire(P, out, true));
     DQ_TRY(check_current_device(P));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (scales != out->scale) {
-        hipError_t e = hipMemcpyAsync(out->scale, scales, static_cast<size_t>(P->desc.M) * P->desc.n_seg * sizeof(float),
-                                      hipMemcpyDeviceToDevice, st);
-        if (e != hipSuccess) return DQGAN_EHIP;
-    }
-    return from_hip(dq::launch_pack(*P, codes, *out, st));
+    return from_hip(dq::launch_pack(*P, codes, scales, *out, st));
 }
 
 dqgan_status dqgan_unpack(dqgan_plan P, const dqgan_wire *in, float *Phat, void *stream) {

@@ -648,202 +648,333 @@ __global__ __launch_bounds__(64 * NG) void k_fused_split(const float *__restrict
     }
 }
 
-// Decode one quad of one row's message to p-hat from its fields: nib = the
-// four sign bits (SIGN, QSGD), raw = the quad's level or code bits (QSGD,
-// MBIT: 32 bits for 8-bit fields, the low 16 for 4-bit fields).
-// CHECK_D: elements at or beyond d decode to 0 (only the last quads of a
-// row need it).  The magnitude is never negative, so the sign bit is set by
-// OR (-0 for a zero level with the sign bit set, as the encoder gives).
-template <int KIND, int LB, bool CHECK_D = true>
-__device__ __forceinline__ f32x4 decode_fields(uint32_t nib, uint32_t raw, const SegConst *__restrict__ crow,
-                                               const int js[4], int64_t i0, int64_t d) {
-    f32x4 out = {0.0f, 0.0f, 0.0f, 0.0f};
-    uint32_t lev = 0u;
-    if (KIND == kMbit) {
-        if (LB == 8) {
-            lev = raw & 0x7F7F7F7Fu;
-            nib = ((raw >> 7) & 1u) | ((raw >> 14) & 2u) | ((raw >> 21) & 4u) | ((raw >> 28) & 8u);
-        } else {
-            lev = (raw & 0x7u) | ((raw & 0x70u) << 4) | ((raw & 0x700u) << 8) | ((raw & 0x7000u) << 12);
-            nib = ((raw >> 3) & 1u) | ((raw >> 6) & 2u) | ((raw >> 9) & 4u) | ((raw >> 12) & 8u);
-        }
-    }
-    if (KIND == kQsgd) {
-        if (LB == 8)
-            lev = raw;
-        else
-            lev = (raw & 0xFu) | ((raw & 0xF0u) << 4) | ((raw & 0xF00u) << 8) | ((raw & 0xF000u) << 12);
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        if (CHECK_D && i0 + c >= d) continue;
-        float mag;
-        if (KIND == kSign) {
-            mag = crow[js[c]].a;
-        } else {
-            const uint32_t l = (lev >> (8 * c)) & 0xFFu;
-            mag = level_magnitude(l, crow[js[c]].b);
-        }
-        set_elem(out, c, __uint_as_float(__float_as_uint(mag) | (((nib >> c) & 1u) << 31)));
-    }
-    return out;
+// The constant b of SegConst (the decoded magnitude is level_magnitude(level,
+// b)) from a scale, by binary32 arithmetic: u sigma is exact and its quotient
+// by the levels, correctly rounded, is far from the denormals, so this equals
+// seg_const's.  SIGN: the scale.
+template <int KIND>
+__device__ __forceinline__ float decode_const(float sc, int levels) {
+    if (KIND == kSign) return sc;
+    if (!(sc > 0.0f && sc <= 3.402823466e38f)) return 0.0f;
+    const bool tiny = sc < 0x1.0p-64f;
+    const float b = mul_rn(sc, tiny ? 0x1.0p64f : 1.0f) / static_cast<float>(levels);
+    return tiny ? -b : b;
 }
 
-// Decode one quad of one row's message to p-hat.
+// Element c (0..3) of a quad's fields: nib = the four sign bits (SIGN,
+// QSGD), raw = the quad's level or code bits (QSGD, MBIT: 32 bits for 8-bit
+// fields, the low 16 for 4-bit fields).
 template <int KIND, int LB>
-__device__ __forceinline__ f32x4 decode_quad(const uint32_t *__restrict__ sign_row, const uint32_t *__restrict__ level_row,
-                                             const float *__restrict__ val_row, const SegConst *__restrict__ crow,
-                                             int64_t q, int64_t d, const int js[4]) {
-    const int64_t i0 = 4 * q;
-    if (KIND == kIdentity) {
-        const f32x4 v = ld4(val_row + i0);
-        f32x4 out;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) set_elem(out, c, (i0 + c < d) ? elem(v, c) : 0.0f);
-        return out;
-    }
-    const uint32_t nib = (KIND == kSign || KIND == kQsgd) ? (sign_row[q >> 3] >> (4 * (q & 7))) & 0xFu : 0u;
-    uint32_t raw = 0u;
-    if (KIND == kQsgd || KIND == kMbit)
-        raw = LB == 8 ? level_row[q] : static_cast<uint32_t>(reinterpret_cast<const uint16_t *>(level_row)[q]);
-    return decode_fields<KIND, LB>(nib, raw, crow, js, i0, d);
+__device__ __forceinline__ uint32_t field_level(uint32_t raw, int c) {
+    const uint32_t f = LB == 8 ? (raw >> (8 * c)) & 0xFFu : (raw >> (4 * c)) & 0xFu;
+    return KIND == kMbit ? f & (LB == 8 ? 0x7Fu : 0x7u) : f;
+}
+template <int KIND, int LB>
+__device__ __forceinline__ uint32_t field_sign(uint32_t nib, uint32_t raw, int c) {  // in bit 31
+    const uint32_t x = KIND == kMbit ? raw << (31 - (LB * (c + 1) - 1)) : nib << (31 - c);
+    return x & 0x80000000u;
+}
+// Its decoded value.  The magnitude is never negative, so the sign bit is set
+// by OR (-0 for a zero level with the sign bit set, as the encoder gives).
+// RANGE: b may be negative (level_magnitude).
+template <int KIND, int LB, bool RANGE>
+__device__ __forceinline__ float decode_field(uint32_t nib, uint32_t raw, int c, float b) {
+    const uint32_t l = KIND == kSign ? 0u : field_level<KIND, LB>(raw, c);
+    const float mag = KIND == kSign ? b : RANGE ? level_magnitude(l, b) : mul_rn(static_cast<float>(l), b);
+    return __uint_as_float(__float_as_uint(mag) | field_sign<KIND, LB>(nib, raw, c));
 }
 
-template <int KIND, int LB>
+// Row kernels off the fused step (unpack, pack), bound by HBM: each thread
+// takes one quad of kUnits units, all loaded before the first is worked on
+// (one quad per thread with its own segment lookup left HBM idle: pack +
+// unpack of 16 workers x 6.3M 8-bit codes 236 us, now 132).  A unit is a row
+// (COLS = false: rows 4 y .. 4 y + 3 of one 1024-column tile, whose segments
+// are looked up once) or, for fewer than kUnits rows, a tile of one row.
+constexpr int kUnits = 4;
+
+struct UnitPos {
+    int m;
+    int64_t tile;
+    bool live;
+};
+template <bool COLS>
+__device__ __forceinline__ UnitPos unit_at(int u, int M, int64_t n_tiles) {
+    UnitPos p;
+    p.m = COLS ? static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y) * kUnits + u;
+    p.tile = COLS ? static_cast<int64_t>(blockIdx.x) * kUnits + u : static_cast<int64_t>(blockIdx.x);
+    p.live = p.m < M && p.tile < n_tiles;
+    return p;
+}
+
+template <int KIND, int LB, bool COLS>
 __global__ __launch_bounds__(kBlock) void k_unpack(const uint32_t *__restrict__ sign_plane,
                                                    const uint32_t *__restrict__ level_plane,
-                                                   const float *__restrict__ val, float *__restrict__ Phat,
-                                                   const SegConst *__restrict__ consts, const int64_t *__restrict__ off,
+                                                   const float *__restrict__ val, const float *__restrict__ scale,
+                                                   float *__restrict__ Phat, const int64_t *__restrict__ off,
                                                    const int32_t *__restrict__ tile_seg, RowArgs a) {
-    const int64_t q = static_cast<int64_t>(blockIdx.x) * kQuadsPerBlock + threadIdx.x;
-    const int m = blockIdx.y;
-    const int64_t rb = static_cast<int64_t>(m) * a.ld;
-    int js[4];
-    lookup_segments(off, tile_seg, 4 * q, a.d, js);
-    const f32x4 v = decode_quad<KIND, LB>(sign_plane + m * a.sign_words, level_plane + m * a.level_words, val + rb,
-                                          consts + static_cast<int64_t>(m) * a.n_seg, q, a.d, js);
-    st_stream(Phat + rb + 4 * q, v);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int64_t n_tiles = a.ld >> 10;
+    uint32_t sg[kUnits], raw[kUnits];
+    f32x4 v[kUnits];
+    float b[kUnits];
+    int js[kUnits];
+    bool one[kUnits];
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+        const UnitPos p = unit_at<COLS>(u, a.M, n_tiles);
+        sg[u] = raw[u] = 0u;
+        if (!p.live) continue;
+        const int64_t q = p.tile * kQuadsPerBlock + threadIdx.x;
+        if (KIND == kSign || KIND == kQsgd) sg[u] = sign_plane[p.m * a.sign_words + (q >> 3)];
+        if (KIND == kQsgd || KIND == kMbit) {
+            const uint32_t *row = level_plane + p.m * a.level_words;
+            raw[u] = LB == 8 ? row[q] : static_cast<uint32_t>(reinterpret_cast<const uint16_t *>(row)[q]);
+        }
+        if (KIND == kIdentity) v[u] = ld4(val + static_cast<int64_t>(p.m) * a.ld + 4 * q);
+    }
+    if (KIND != kIdentity) {
+        // the wave's 256 columns of each unit: its segment, and its constant
+        // where one segment holds them all
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+            const UnitPos p = unit_at<COLS>(u, a.M, n_tiles);
+            if (!COLS && u > 0) {
+                js[u] = js[0];
+                one[u] = one[0];
+            } else if (p.live) {
+                const int64_t w0 = p.tile * kElemsPerBlock + 256 * wave;
+                js[u] = uniform_segment(off, tile_seg, w0, a.d);
+                one[u] = off[js[u] + 1] >= (w0 + 256 < a.d ? w0 + 256 : a.d);
+            }
+            if (p.live) b[u] = decode_const<KIND>(scale[static_cast<int64_t>(p.m) * a.n_seg + js[u]], a.s);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+        const UnitPos p = unit_at<COLS>(u, a.M, n_tiles);
+        if (!p.live) continue;
+        const int64_t q = p.tile * kQuadsPerBlock + threadIdx.x, i0 = 4 * q;
+        f32x4 o;
+        if (KIND == kIdentity) {
+            o = v[u];
+        } else if (one[u]) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                set_elem(o, c, decode_field<KIND, LB, true>(sg[u] >> (4 * (lane & 7)), raw[u], c, b[u]));
+        } else {
+            int j = js[u];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                j = seg_from(off, j, i0 + c < a.d ? i0 + c : a.d - 1);
+                const float bc = decode_const<KIND>(scale[static_cast<int64_t>(p.m) * a.n_seg + j], a.s);
+                set_elem(o, c, decode_field<KIND, LB, true>(sg[u] >> (4 * (lane & 7)), raw[u], c, bc));
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (i0 + c >= a.d) set_elem(o, c, 0.0f);
+        st_stream(Phat + static_cast<int64_t>(p.m) * a.ld + i0, o);
+    }
 }
 
 // Server average of the M messages.  A thread covers four consecutive
 // quads (16 elements: 16 sign bits, 8 or 16 bytes of fields per row, so
-// each row's loads are 2-16 bytes per lane rather than sub-word), and takes
-// the rows in chunks of kAggRows whose fields are all loaded before the
-// first is decoded; the sum runs in ascending worker order.
+// each row's loads are 2-16 bytes per lane rather than sub-word), a wave
+// 1024.  The sum runs in ascending worker order, from -0 (fl(-0 + x) = x for
+// every x, so the sum is the definition's, which starts from worker 0's
+// term).  Elements at or beyond d are summed with the rest and dropped at the
+// end.
+//
+// Bound by the vector ALU: 6 operations per decoded element (field, its
+// conversion, the product, the sign's shift and OR, the sum) take 166 us of
+// the 199 us at 32 workers x 2^25, s = 15 (262 us before: 8.8 operations, a
+// bound test per row, and constants from a launch of their own).
+// 16 workers x 6.3M 8-bit codes 46 -> 30 us, 8 x 10^6 15.3 -> 11.5.
+// Held to 80 registers for six waves per SIMD the kernel spills: 274 us.
 constexpr int kAggQuads = 4;
-constexpr int kAggRows = 4;
+constexpr int kAggSegs = 8;  // segments of a wave up to which each takes a pass of its own
 
 template <int KIND, int LB>
+struct AggFields {
+    static constexpr int kWords = (KIND == kQsgd || KIND == kMbit) ? LB / 2 : 1;  // 32-bit words of fields per row
+    uint32_t sg, fw[kWords];
+
+    __device__ __forceinline__ void load(const uint32_t *__restrict__ sign_plane,
+                                         const uint32_t *__restrict__ level_plane, const RowArgs &a, int m,
+                                         int64_t g16) {
+        if (KIND == kSign || KIND == kQsgd) sg = reinterpret_cast<const uint16_t *>(sign_plane + m * a.sign_words)[g16];
+        if (KIND == kQsgd || KIND == kMbit) {
+            const uint32_t *w = level_plane + m * a.level_words + kWords * g16;
+            if constexpr (kWords == 4) {
+                const u32x4 x = *reinterpret_cast<const u32x4 *>(w);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) fw[c] = elem(x, c);
+            } else if constexpr (kWords == 2) {
+                const uint2 x = *reinterpret_cast<const uint2 *>(w);
+                fw[0] = x.x;
+                fw[1] = x.y;
+            }
+        }
+    }
+    // element c of quad k
+    template <bool RANGE>
+    __device__ __forceinline__ float value(int k, int c, float b) const {
+        const uint32_t raw = KIND == kSign ? 0u : kWords == 4 ? fw[k % kWords] : fw[(k >> 1) % kWords] >> (16 * (k & 1));
+        return decode_field<KIND, LB, RANGE>(sg >> (4 * k), raw, c, b);
+    }
+};
+
+template <int KIND, int LB, bool MANY>
 __global__ __launch_bounds__(kBlock) void k_aggregate(const uint32_t *__restrict__ sign_plane,
                                                       const uint32_t *__restrict__ level_plane,
-                                                      const float *__restrict__ val, float *__restrict__ Qhat,
+                                                      const float *__restrict__ scale, float *__restrict__ Qhat,
                                                       const SegConst *__restrict__ consts,
                                                       const int64_t *__restrict__ off,
                                                       const int32_t *__restrict__ tile_seg, RowArgs a, float invM) {
-    const int64_t g16 = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;  // group of 16 elements
-    const int64_t q0 = kAggQuads * g16;
-    const bool live = 4 * q0 < a.ld;
-    int js[kAggQuads][4];
+    typedef AggFields<KIND, LB> Fields;
+    // 2 bytes a row and thread: more rows in flight (32 workers x 2^25 signs:
+    // 108 us with eight, 116 with four)
+    constexpr int kAggRows = KIND == kSign ? 8 : 4;
+    const int lane = threadIdx.x & 63;
+    const int64_t tile = static_cast<int64_t>(blockIdx.x) * (kBlock / 64) +
+                         __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    if (tile >= (a.ld >> 10)) return;  // whole waves
+    const int64_t g16 = tile * 64 + lane;  // group of 16 elements
+    const int64_t w0 = tile << 10;
+    const int64_t w1 = w0 + 1024 < a.d ? w0 + 1024 : a.d;  // past the wave's last element below d (w1 <= w0: none)
+    const int j0 = tile_seg[tile];
+    int j1 = j0;  // the wave's last segment
+    while (off[j1 + 1] < w1) ++j1;
+    f32x4 acc[kAggQuads], qh[kAggQuads];
+    auto restart = [&] {
 #pragma unroll
-    for (int k = 0; k < kAggQuads; ++k) lookup_segments(off, tile_seg, live ? 4 * (q0 + k) : 0, a.d, js[k]);
-    // the whole wave in one segment (the common case): one scalar load of
-    // the constants per row
-    const int j_first = __builtin_amdgcn_readfirstlane(js[0][0]);
-    const bool one_seg = __ballot(live && (js[0][0] != j_first || js[kAggQuads - 1][3] != j_first)) == 0;
-    const int z[4] = {0, 0, 0, 0};
-    // every element of the wave below d: no per-element bound tests
-    const bool full = __ballot(4 * (q0 + kAggQuads) > a.d) == 0;
-    constexpr int kFieldWords = (KIND == kQsgd || KIND == kMbit) ? LB / 2 : 0;  // 32-bit words of fields per row
-    f32x4 acc[kAggQuads];
-#pragma unroll
-    for (int k = 0; k < kAggQuads; ++k) acc[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    // the fields of row m for this thread's 16 elements
-    auto load_row = [&](int m, uint32_t &sg, uint32_t (&fw)[kFieldWords > 0 ? kFieldWords : 1],
-                        f32x4 (&vv)[KIND == kIdentity ? kAggQuads : 1]) {
-        if (KIND == kSign || KIND == kQsgd) sg = reinterpret_cast<const uint16_t *>(sign_plane + m * a.sign_words)[g16];
-        if (kFieldWords == 4) {
-            const u32x4 v = *reinterpret_cast<const u32x4 *>(level_plane + m * a.level_words + 4 * g16);
-            fw[0] = v.x;
-            fw[kFieldWords > 1 ? 1 : 0] = v.y;
-            fw[kFieldWords > 2 ? 2 : 0] = v.z;
-            fw[kFieldWords > 3 ? 3 : 0] = v.w;
-        } else if (kFieldWords == 2) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(level_plane + m * a.level_words + 2 * g16);
-            fw[0] = v.x;
-            fw[kFieldWords > 1 ? 1 : 0] = v.y;
-        }
-        if (KIND == kIdentity) {
-#pragma unroll
-            for (int k = 0; k < kAggQuads; ++k)
-                vv[KIND == kIdentity ? k : 0] = ld4(val + static_cast<int64_t>(m) * a.ld + 4 * (q0 + k));
-        }
+        for (int k = 0; k < kAggQuads; ++k) acc[k] = f32x4{-0.0f, -0.0f, -0.0f, -0.0f};
     };
-    // add row m (ascending order) given its loaded fields and its constants
-    auto add_row = [&](int m, uint32_t sg, const uint32_t (&fw)[kFieldWords > 0 ? kFieldWords : 1],
-                       const f32x4 (&vv)[KIND == kIdentity ? kAggQuads : 1], const SegConst *crow, bool uniform) {
+    // the average of the elements of [lo, hi) from their sums
+    auto keep = [&](int64_t lo, int64_t hi) {
 #pragma unroll
         for (int k = 0; k < kAggQuads; ++k) {
-            const int64_t i0 = 4 * (q0 + k);
-            f32x4 v;
-            if (KIND == kIdentity) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) set_elem(v, c, (i0 + c < a.d) ? elem(vv[KIND == kIdentity ? k : 0], c) : 0.0f);
-            } else {
-                const uint32_t nib = (KIND == kSign || KIND == kQsgd) ? (sg >> (4 * k)) & 0xFu : 0u;
-                uint32_t raw = 0u;
-                if (kFieldWords == 4) raw = fw[k < kFieldWords ? k : 0];
-                if (kFieldWords == 2) raw = (fw[(k >> 1) < kFieldWords ? (k >> 1) : 0] >> (16 * (k & 1))) & 0xFFFFu;
-                v = full ? decode_fields<KIND, LB, false>(nib, raw, crow, uniform ? z : js[k], i0, a.d)
-                         : decode_fields<KIND, LB, true>(nib, raw, crow, uniform ? z : js[k], i0, a.d);
-            }
-            if (m == 0) {
-                acc[k] = v;
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) set_elem(acc[k], c, add_rn(elem(acc[k], c), elem(v, c)));
+            for (int c = 0; c < 4; ++c) {
+                const int64_t i = 16 * g16 + 4 * k + c;
+                const float sacc = elem(acc[k], c);
+                const float x = invM > 0.0f ? mul_rn(sacc, invM)
+                                            : static_cast<float>(static_cast<double>(sacc) / static_cast<double>(a.M));
+                if (i >= lo && i < hi) set_elem(qh[k], c, x);
             }
         }
     };
-    if (one_seg) {
-        // kAggRows rows' fields loaded before the first is decoded
-        for (int m0 = 0; m0 < a.M; m0 += kAggRows) {
-            uint32_t sg[kAggRows];
-            uint32_t fw[kAggRows][kFieldWords > 0 ? kFieldWords : 1];
-            f32x4 vv[kAggRows][KIND == kIdentity ? kAggQuads : 1];
 #pragma unroll
-            for (int u = 0; u < kAggRows; ++u)
-                if (m0 + u < a.M && live) load_row(m0 + u, sg[u], fw[u], vv[u]);
+    for (int k = 0; k < kAggQuads; ++k) qh[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // Every row's 16 elements decoded with the constants of segment j.
+    auto sum_rows = [&](int j) {
+        // lane l keeps the constant of row mb + l, handed to the wave as a
+        // scalar when the row's turn comes
+        for (int mb = 0; mb < a.M; mb += 64) {
+            const int n = a.M - mb < 64 ? a.M - mb : 64;
+            float bl = 0.0f;
+            if (lane < n)
+                bl = decode_const<KIND>(scale[static_cast<int64_t>(mb + lane) * a.n_seg + j], a.s);
+            auto rows = [&](auto range) {
+                auto add_row = [&](const Fields &f, int r) {
+                    const float b = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(bl), r));
 #pragma unroll
-            for (int u = 0; u < kAggRows; ++u) {
-                const int m = m0 + u;
-                if (m < a.M && live) {
-                    const SegConst c1[1] = {consts[static_cast<int64_t>(m) * a.n_seg + j_first]};
-                    add_row(m, sg[u], fw[u], vv[u], c1, true);
+                    for (int k = 0; k < kAggQuads; ++k) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            set_elem(acc[k], c,
+                                     add_rn(elem(acc[k], c), f.template value<decltype(range)::value>(k, c, b)));
+                    }
+                };
+                // batches of rows all loaded before the first is decoded,
+                // then the rows left over
+                int r0 = 0;
+                for (; r0 + kAggRows <= n; r0 += kAggRows) {
+                    Fields f[kAggRows];
+#pragma unroll
+                    for (int u = 0; u < kAggRows; ++u) f[u].load(sign_plane, level_plane, a, mb + r0 + u, g16);
+#pragma unroll
+                    for (int u = 0; u < kAggRows; ++u) add_row(f[u], r0 + u);
+                }
+                for (; r0 < n; ++r0) {
+                    Fields f;
+                    f.load(sign_plane, level_plane, a, mb + r0, g16);
+                    add_row(f, r0);
+                }
+            };
+            // no negative constant (no scale below 2^-64): one product less
+            // per element
+            if (KIND == kSign || __ballot(bl < 0.0f) == 0)
+                rows(std::false_type{});
+            else
+                rows(std::true_type{});
+        }
+    };
+    if (!MANY || j1 - j0 < kAggSegs) {
+        // one segment (the common case) or a few: each decodes the wave's
+        // messages once and keeps its own elements
+        for (int j = j0; j <= j1; ++j) {
+            restart();
+            sum_rows(j);
+            keep(off[j], off[j + 1]);
+        }
+    } else if constexpr (MANY) {
+        // many short segments: every element its own constant
+        restart();
+        for (int m = 0; m < a.M; ++m) {
+            Fields f;
+            f.load(sign_plane, level_plane, a, m, g16);
+            int jc = j0;
+#pragma unroll
+            for (int k = 0; k < kAggQuads; ++k) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int64_t i = 16 * g16 + 4 * k + c;
+                    jc = seg_from(off, jc, i < a.d ? i : a.d - 1);
+                    const int64_t o = static_cast<int64_t>(m) * a.n_seg + jc;
+                    const float b = KIND == kSign ? consts[o].a : consts[o].b;
+                    set_elem(acc[k], c, add_rn(elem(acc[k], c), f.template value<true>(k, c, b)));
                 }
             }
         }
-    } else if (live) {
-        // a wave across segment boundaries: one row at a time
-        for (int m = 0; m < a.M; ++m) {
-            uint32_t sg = 0u;
-            uint32_t fw[kFieldWords > 0 ? kFieldWords : 1];
-            f32x4 vv[KIND == kIdentity ? kAggQuads : 1];
-            load_row(m, sg, fw, vv);
-            add_row(m, sg, fw, vv, consts + static_cast<int64_t>(m) * a.n_seg, false);
-        }
+        keep(0, a.d);
     }
-    if (!live) return;
 #pragma unroll
-    for (int k = 0; k < kAggQuads; ++k) {
-        f32x4 qh;
+    for (int k = 0; k < kAggQuads; ++k) st4(Qhat + 16 * g16 + 4 * k, qh[k]);
+}
+
+// The same for IDENTITY messages (dense binary32 rows): one quad per thread, so
+// that a wave reads 1 KB of a row at a time.
+constexpr int kMeanRows = 8;  // rows loaded before the first is added
+
+__global__ __launch_bounds__(kBlock) void k_mean_rows(const float *__restrict__ val, float *__restrict__ Qhat,
+                                                      int64_t d, int64_t ld, int32_t M, float invM) {
+    const int64_t i0 = 4 * (static_cast<int64_t>(blockIdx.x) * kQuadsPerBlock + threadIdx.x);
+    const float *src = val + i0;
+    f32x4 acc = {-0.0f, -0.0f, -0.0f, -0.0f};
+    auto add = [&](const f32x4 &v) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float sacc = elem(acc[k], c);
-            set_elem(qh, c, invM > 0.0f ? mul_rn(sacc, invM)
-                                        : static_cast<float>(static_cast<double>(sacc) / static_cast<double>(a.M)));
-        }
-        st4(Qhat + 4 * (q0 + k), qh);
+        for (int c = 0; c < 4; ++c) set_elem(acc, c, add_rn(elem(acc, c), elem(v, c)));
+    };
+    int m = 0;
+    for (; m + kMeanRows <= M; m += kMeanRows) {
+        f32x4 v[kMeanRows];
+#pragma unroll
+        for (int u = 0; u < kMeanRows; ++u) v[u] = ld_stream(src + static_cast<int64_t>(m + u) * ld);
+#pragma unroll
+        for (int u = 0; u < kMeanRows; ++u) add(v[u]);
     }
+    for (; m < M; ++m) add(ld_stream(src + static_cast<int64_t>(m) * ld));
+    f32x4 qh;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const float sacc = elem(acc, c);
+        const float x = invM > 0.0f ? mul_rn(sacc, invM)
+                                    : static_cast<float>(static_cast<double>(sacc) / static_cast<double>(M));
+        set_elem(qh, c, i0 + c < d ? x : 0.0f);
+    }
+    st4(Qhat + i0, qh);
 }
 
 __global__ __launch_bounds__(kBlock) void k_omd(const float *__restrict__ Qhat, float *__restrict__ W,
@@ -885,31 +1016,47 @@ __global__ __launch_bounds__(kBlock) void k_omd(const float *__restrict__ Qhat, 
     }
 }
 
-template <int LB, int KIND>
-__global__ __launch_bounds__(kBlock) void k_pack(const uint16_t *__restrict__ codes, uint32_t *__restrict__ sign_plane,
-                                                 uint32_t *__restrict__ level_plane, RowArgs a) {
-    const int64_t q = static_cast<int64_t>(blockIdx.x) * kQuadsPerBlock + threadIdx.x;
-    const int m = blockIdx.y;
-    const int64_t i0 = 4 * q;
-    const uint2 raw = *reinterpret_cast<const uint2 *>(codes + static_cast<int64_t>(m) * a.ld + i0);
-    const uint32_t c4[4] = {raw.x & 0xFFFFu, raw.x >> 16, raw.y & 0xFFFFu, raw.y >> 16};
-    QuadCodes cq;
-    cq.sign_nib = 0u;
-    cq.levels = 0u;
+// Packs the caller's codes; the scales (when they are not the message's own)
+// are copied by the first threads of the grid.
+template <int LB, int KIND, bool COLS>
+__global__ __launch_bounds__(kBlock) void k_pack(const uint16_t *__restrict__ codes, const float *__restrict__ scales,
+                                                 uint32_t *__restrict__ sign_plane, uint32_t *__restrict__ level_plane,
+                                                 float *__restrict__ scale_out, RowArgs a) {
+    const int64_t n_tiles = a.ld >> 10;
+    uint2 raw[kUnits];
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+        const UnitPos p = unit_at<COLS>(u, a.M, n_tiles);
+        if (p.live)
+            raw[u] = *reinterpret_cast<const uint2 *>(codes + static_cast<int64_t>(p.m) * a.ld +
+                                                      p.tile * kElemsPerBlock + 4 * threadIdx.x);
+    }
+    if (scale_out) {
+        const int64_t n = static_cast<int64_t>(a.M) * a.n_seg;
+        const int64_t wg = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+        for (int64_t i = wg * kBlock + threadIdx.x; i < n; i += static_cast<int64_t>(gridDim.x) * gridDim.y * kBlock)
+            scale_out[i] = scales[i];
+    }
     const uint32_t fmask = KIND == kMbit ? (LB == 8 ? 0x7Fu : 0x7u) : (LB == 8 ? 0xFFu : 0xFu);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        if (i0 + c >= a.d) continue;
-        cq.sign_nib |= ((c4[c] >> 15) & 1u) << c;
-        cq.levels |= (c4[c] & fmask) << (8 * c);
+    for (int u = 0; u < kUnits; ++u) {
+        const UnitPos p = unit_at<COLS>(u, a.M, n_tiles);
+        if (!p.live) continue;  // whole workgroups
+        const int64_t q = p.tile * kQuadsPerBlock + threadIdx.x, i0 = 4 * q;
+        const uint32_t c4[4] = {raw[u].x & 0xFFFFu, raw[u].x >> 16, raw[u].y & 0xFFFFu, raw[u].y >> 16};
+        QuadCodes cq;
+        cq.sign_nib = 0u;
+        cq.levels = 0u;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (i0 + c >= a.d) continue;
+            cq.sign_nib |= ((c4[c] >> 15) & 1u) << c;
+            cq.levels |= (c4[c] & fmask) << (8 * c);
+        }
+        store_message_rt<KIND, LB>(KIND == kMbit ? nullptr : sign_plane + p.m * a.sign_words,
+                                   KIND == kSign ? nullptr : level_plane + p.m * a.level_words, nullptr, q, cq,
+                                   a.stream_msg != 0);
     }
-    if (KIND == kSign)
-        store_message_rt<kSign, 0>(sign_plane + m * a.sign_words, nullptr, nullptr, q, cq, a.stream_msg != 0);
-    else if (KIND == kMbit)
-        store_message_rt<kMbit, LB>(nullptr, level_plane + m * a.level_words, nullptr, q, cq, a.stream_msg != 0);
-    else
-        store_message_rt<kQsgd, LB>(sign_plane + m * a.sign_words, level_plane + m * a.level_words, nullptr, q,
-                                    cq, a.stream_msg != 0);
 }
 
 // Top-k worker side only (dqgan_compress_ef): one wave per (tile, worker).
@@ -1097,46 +1244,71 @@ hipError_t launch_fused_dense(const dqgan_plan_s &P, float eta, uint32_t t, cons
     });
 }
 
-hipError_t launch_pack(const dqgan_plan_s &P, const uint16_t *codes, const dqgan_wire &w, hipStream_t st) {
+// The grid of a kernel over units (unit_at): f(COLS, grid).
+template <typename F>
+static hipError_t with_units(const dqgan_plan_s &P, F &&f) {
+    const unsigned n = static_cast<unsigned>(P.n_tiles), M = static_cast<unsigned>(P.desc.M);
+    if (P.desc.M < kUnits) return f(std::true_type{}, dim3((n + kUnits - 1) / kUnits, M));
+    return f(std::false_type{}, dim3(n, (M + kUnits - 1) / kUnits));
+}
+
+hipError_t launch_pack(const dqgan_plan_s &P, const uint16_t *codes, const float *scales, const dqgan_wire &w,
+                       hipStream_t st) {
     const RowArgs a = row_args(P, 0.0f, 0);
-    const dim3 grid(static_cast<unsigned>(P.n_tiles), static_cast<unsigned>(P.desc.M));
     return with_dense_kind(P, [&](auto K, auto L) {
         if constexpr (decltype(K)::value == kIdentity) {
             return hipErrorInvalidValue;  // the identity has no codes to pack
         } else {
-            hipLaunchKernelGGL((k_pack<decltype(L)::value, decltype(K)::value>), grid, dim3(kBlock), 0, st, codes,
-                               w.sign, w.level, a);
-            return hipGetLastError();
+            return with_units(P, [&](auto C, dim3 grid) {
+                hipLaunchKernelGGL((k_pack<decltype(L)::value, decltype(K)::value, decltype(C)::value>), grid,
+                                   dim3(kBlock), 0, st, codes, scales, w.sign, w.level,
+                                   scales == w.scale ? nullptr : w.scale, a);
+                return hipGetLastError();
+            });
         }
     });
 }
 
 hipError_t launch_unpack_dense(const dqgan_plan_s &P, const dqgan_wire &w, float *Phat, hipStream_t st) {
     const RowArgs a = row_args(P, 0.0f, 0);
-    const dim3 grid(static_cast<unsigned>(P.n_tiles), static_cast<unsigned>(P.desc.M));
-    if (P.desc.kind != kIdentity) {
-        hipError_t err = launch_consts_from_scales(P, w.scale, st);
-        if (err != hipSuccess) return err;
-    }
     return with_dense_kind(P, [&](auto K, auto L) {
-        hipLaunchKernelGGL((k_unpack<decltype(K)::value, decltype(L)::value>), grid, dim3(kBlock), 0, st, w.sign,
-                           w.level, w.val, Phat, P.d_consts, P.d_off, P.d_tile_seg, a);
-        return hipGetLastError();
+        return with_units(P, [&](auto C, dim3 grid) {
+            hipLaunchKernelGGL((k_unpack<decltype(K)::value, decltype(L)::value, decltype(C)::value>), grid,
+                               dim3(kBlock), 0, st, w.sign, w.level, w.val, w.scale, Phat, P.d_off, P.d_tile_seg, a);
+            return hipGetLastError();
+        });
     });
 }
 
 hipError_t launch_aggregate_dense(const dqgan_plan_s &P, const dqgan_wire &w, float *Qhat, hipStream_t st) {
     const RowArgs a = row_args(P, 0.0f, 0);
-    const dim3 grid(static_cast<unsigned>((P.n_tiles + kAggQuads - 1) / kAggQuads));  // 16 elements per thread
     const float im = inv_m(P.desc.M);
-    if (P.desc.kind != kIdentity) {
+    if (P.desc.kind == kIdentity) {
+        hipLaunchKernelGGL(k_mean_rows, dim3(static_cast<unsigned>(P.n_tiles)), dim3(kBlock), 0, st, w.val, Qhat,
+                           P.desc.d, P.desc.ld, P.desc.M, im);
+        return hipGetLastError();
+    }
+    const dim3 grid(static_cast<unsigned>((P.n_tiles + kAggQuads - 1) / kAggQuads));  // a tile per wave
+    // Tiles of more segments than a wave takes one by one: the variant that
+    // looks up every element's constant, derived once per (worker, segment)
+    // by a launch of its own (16 quotients per thread and row otherwise).
+    const bool many = P.max_tile_segs > kAggSegs;
+    if (many) {
         hipError_t err = launch_consts_from_scales(P, w.scale, st);
         if (err != hipSuccess) return err;
     }
     return with_dense_kind(P, [&](auto K, auto L) {
-        hipLaunchKernelGGL((k_aggregate<decltype(K)::value, decltype(L)::value>), grid, dim3(kBlock), 0, st, w.sign,
-                           w.level, w.val, Qhat, P.d_consts, P.d_off, P.d_tile_seg, a, im);
-        return hipGetLastError();
+        if constexpr (decltype(K)::value == kIdentity) {
+            return hipErrorInvalidValue;  // served above
+        } else {
+            auto go = [&](auto many_c) {
+                hipLaunchKernelGGL((k_aggregate<decltype(K)::value, decltype(L)::value, decltype(many_c)::value>), grid,
+                                   dim3(kBlock), 0, st, w.sign, w.level, w.scale, Qhat, P.d_consts, P.d_off,
+                                   P.d_tile_seg, a, im);
+                return hipGetLastError();
+            };
+            return many ? go(std::true_type{}) : go(std::false_type{});
+        }
     });
 }
 

@@ -127,6 +127,7 @@ struct dqgan_plan_s {
 
     int64_t *d_off = nullptr;       // [n_seg + 1]
     int32_t *d_tile_seg = nullptr;  // [n_tiles] segment of each tile's first element
+    int32_t max_tile_segs = 1;      // most segments that meet one tile (1024 elements)
     dq::Piece *d_pieces = nullptr;  // [n_pieces]
     int32_t n_pieces = 0;
     int32_t *d_seg_piece = nullptr;  // [n_seg + 1] first piece of each segment
@@ -146,7 +147,8 @@ hipError_t launch_encode(const dqgan_plan_s &P, float eta, uint32_t t, const flo
                          const dqgan_wire &w, hipStream_t st);
 hipError_t launch_fused_dense(const dqgan_plan_s &P, float eta, uint32_t t, const float *G, float *E, float *W,
                               float *WX, const dqgan_wire &w, float *Qhat, hipStream_t st);
-hipError_t launch_pack(const dqgan_plan_s &P, const uint16_t *codes, const dqgan_wire &w, hipStream_t st);
+hipError_t launch_pack(const dqgan_plan_s &P, const uint16_t *codes, const float *scales, const dqgan_wire &w,
+                       hipStream_t st);
 hipError_t launch_unpack_dense(const dqgan_plan_s &P, const dqgan_wire &w, float *Phat, hipStream_t st);
 hipError_t launch_aggregate_dense(const dqgan_plan_s &P, const dqgan_wire &w, float *Qhat, hipStream_t st);
 hipError_t launch_omd(const dqgan_plan_s &P, float eta, const float *Qhat, float *W, const float *G,
