@@ -16,6 +16,7 @@
 //      w_t = w_{t-1} - q-hat; every wave then writes its rows' evaluation
 //      points w_t - (fl(eta g) + e_t).  k_fused (one lane walks all M rows)
 //      serves M > 128.
+#include <algorithm>
 #include <type_traits>
 
 #include "device.hpp"
@@ -525,7 +526,10 @@ __global__ __launch_bounds__(kBlock) void k_fused(const float *__restrict__ G, f
 // 0..g-1, so the result is the same sequential binary32 sum as in the
 // one-lane-per-quad kernel.  Few registers per lane leave room for many
 // waves per SIMD, which keeps enough loads in flight to stream from HBM.
-template <int KIND, int LB, int R, int NG, bool STREAM>
+// NB > 1 (more rows than the waves can keep at once): the waves take NB
+// blocks of NG R rows in turn, the chain going on from block to block; only
+// the extrapolation operands of the earlier blocks stay in registers.
+template <int KIND, int LB, int R, int NG, int NB, bool STREAM>
 __global__ __launch_bounds__(64 * NG) void k_fused_split(const float *__restrict__ G, float *__restrict__ E,
                                                          float *__restrict__ W, float *__restrict__ WX,
                                                          float *__restrict__ Qhat, uint32_t *__restrict__ sign_plane,
@@ -538,7 +542,7 @@ __global__ __launch_bounds__(64 * NG) void k_fused_split(const float *__restrict
     const int lane = threadIdx.x & 63;
     const int g = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int M = a.M;
-    const int last_g = (M - 1) / R;  // the wave that finishes the sum
+    const int last = (M - 1) / R;  // the link of the chain that finishes the sum
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 64 + lane;
     const int64_t i0 = 4 * q;
     // One row per wave (every wave that is launched owns one): its loads go
@@ -559,85 +563,89 @@ __global__ __launch_bounds__(64 * NG) void k_fused_split(const float *__restrict
     const bool one_seg = KIND == kTopk || KIND == kIdentity || off[j_first + 1] >= c1;
     int js[4] = {j_first, j_first, j_first, j_first};
     if (!one_seg) lookup_segments(off, tile_seg, i0, a.d, js);
-    f32x4 ph[R], xs[R];
+    f32x4 ph[R], xs[NB * R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int m = g * R + r;
-        if (m < M) {
-            const int64_t rb = static_cast<int64_t>(m) * a.ld;
-            const f32x4 gv = R == 1 ? g_first : ld_stream(G + rb + i0);
-            const f32x4 ev = R == 1 ? e_first : ld_stream(E + rb + i0);
-            const SegConst *crow = consts + static_cast<int64_t>(m) * a.n_seg;
-            QuadCodes cq;
-            if constexpr (KIND == kTopk) {
-                const TopkRow *rw = ta.rows + m;
-                cq = encode_quad_topk(gv, ev, a.eta, i0, a.d, rw->T, rw->I);
-            } else if (one_seg) {
-                const SegConst cu = crow[j_first];
-                const SegConst c4[1] = {cu};
-                const int z[4] = {0, 0, 0, 0};
-                cq = encode_quad<KIND>(gv, ev, a.eta, i0, a.d, m, z, c4, a.s, a.k0, a.k1, a.t);
-            } else {
-                cq = encode_quad<KIND>(gv, ev, a.eta, i0, a.d, m, js, crow, a.s, a.k0, a.k1, a.t);
-            }
-            st_stream(E + rb + i0, cq.enew);
-            if constexpr (KIND == kTopk) {
-                store_topk(val + m * ta.k, ta.idx + m * ta.k, ta.k, topk_tile_base(ta, m, blockIdx.x), i0, cq);
-            } else {
-                store_message<KIND, LB, STREAM>(sign_plane + m * a.sign_words, level_plane + m * a.level_words,
-                                                val + rb, q, cq);
-            }
-            ph[r] = cq.phat;
+    for (int nb = 0; nb < NB; ++nb) {
+        if (nb > 0 && nb * NG > last) break;  // uniform: no row left
 #pragma unroll
-            for (int c = 0; c < 4; ++c) set_elem(xs[r], c, add_rn(elem(cq.eg, c), elem(cq.enew, c)));
+        for (int r = 0; r < R; ++r) {
+            const int m = (nb * NG + g) * R + r;
+            if (m < M) {
+                const int64_t rb = static_cast<int64_t>(m) * a.ld;
+                const f32x4 gv = R == 1 ? g_first : ld_stream(G + rb + i0);
+                const f32x4 ev = R == 1 ? e_first : ld_stream(E + rb + i0);
+                const SegConst *crow = consts + static_cast<int64_t>(m) * a.n_seg;
+                QuadCodes cq;
+                if constexpr (KIND == kTopk) {
+                    const TopkRow *rw = ta.rows + m;
+                    cq = encode_quad_topk(gv, ev, a.eta, i0, a.d, rw->T, rw->I);
+                } else if (one_seg) {
+                    const SegConst cu = crow[j_first];
+                    const SegConst c4[1] = {cu};
+                    const int z[4] = {0, 0, 0, 0};
+                    cq = encode_quad<KIND>(gv, ev, a.eta, i0, a.d, m, z, c4, a.s, a.k0, a.k1, a.t);
+                } else {
+                    cq = encode_quad<KIND>(gv, ev, a.eta, i0, a.d, m, js, crow, a.s, a.k0, a.k1, a.t);
+                }
+                st_stream(E + rb + i0, cq.enew);
+                if constexpr (KIND == kTopk) {
+                    store_topk(val + m * ta.k, ta.idx + m * ta.k, ta.k, topk_tile_base(ta, m, blockIdx.x), i0, cq);
+                } else {
+                    store_message<KIND, LB, STREAM>(sign_plane + m * a.sign_words, level_plane + m * a.level_words,
+                                                    val + rb, q, cq);
+                }
+                ph[r] = cq.phat;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) set_elem(xs[nb * R + r], c, add_rn(elem(cq.eg, c), elem(cq.enew, c)));
+            }
         }
-    }
 #pragma unroll
-    for (int phase = 0; phase < NG; ++phase) {
-        if (phase <= last_g) {
-            if (g == phase) {
-                f32x4 acc;
-                if (phase == 0) {
-                    acc = ph[0];
-                } else {
-                    acc = chain[lane];
+        for (int phase = 0; phase < NG; ++phase) {
+            if (nb * NG + phase <= last) {
+                if (g == phase) {
+                    f32x4 acc;
+                    if (nb == 0 && phase == 0) {
+                        acc = ph[0];
+                    } else {
+                        acc = chain[lane];
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) set_elem(acc, c, add_rn(elem(acc, c), elem(ph[0], c)));
-                }
+                        for (int c = 0; c < 4; ++c) set_elem(acc, c, add_rn(elem(acc, c), elem(ph[0], c)));
+                    }
 #pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    if (g * R + r < M) {
+                    for (int r = 1; r < R; ++r) {
+                        if ((nb * NG + g) * R + r < M) {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) set_elem(acc, c, add_rn(elem(acc, c), elem(ph[r], c)));
+                            for (int c = 0; c < 4; ++c) set_elem(acc, c, add_rn(elem(acc, c), elem(ph[r], c)));
+                        }
+                    }
+                    if (nb * NG + phase < last) {
+                        chain[lane] = acc;
+                    } else {
+                        f32x4 qh;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const float sacc = elem(acc, c);
+                            set_elem(qh, c, invM > 0.0f ? mul_rn(sacc, invM)
+                                                        : static_cast<float>(static_cast<double>(sacc) /
+                                                                             static_cast<double>(M)));
+                        }
+                        const f32x4 w = ld4(W + i0);
+                        f32x4 wt;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) set_elem(wt, c, sub_rn(elem(w, c), elem(qh, c)));
+                        st4(W + i0, wt);
+                        if (Qhat) st4(Qhat + i0, qh);
+                        chain[lane] = wt;
                     }
                 }
-                if (phase < last_g) {
-                    chain[lane] = acc;
-                } else {
-                    f32x4 qh;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const float sacc = elem(acc, c);
-                        set_elem(qh, c, invM > 0.0f ? mul_rn(sacc, invM)
-                                                    : static_cast<float>(static_cast<double>(sacc) /
-                                                                         static_cast<double>(M)));
-                    }
-                    const f32x4 w = ld4(W + i0);
-                    f32x4 wt;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) set_elem(wt, c, sub_rn(elem(w, c), elem(qh, c)));
-                    st4(W + i0, wt);
-                    if (Qhat) st4(Qhat + i0, qh);
-                    chain[lane] = wt;
-                }
+                __syncthreads();
             }
-            __syncthreads();
         }
     }
     const f32x4 wt = chain[lane];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int m = g * R + r;
+    for (int r = 0; r < NB * R; ++r) {
+        const int m = ((r / R) * NG + g) * R + r % R;
         if (m < M) {
             const int64_t rb = static_cast<int64_t>(m) * a.ld;
             f32x4 wx;
@@ -1131,13 +1139,13 @@ constexpr unsigned cap_lds(int R, int NG) {
     return NG != 8 ? 0u : R == 2 ? 52000u : R == 4 ? 79000u : 0u;
 }
 
-template <int KIND, int LB, int R, int NG>
+template <int KIND, int LB, int R, int NG, int NB = 1>
 hipError_t split_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G, float *E, float *W, float *WX,
                         const dqgan_wire &w, float *Qhat, hipStream_t st) {
-    if (P.desc.M > R * NG) return hipErrorInvalidValue;  // every worker must belong to a wave
+    if (P.desc.M > R * NG * NB) return hipErrorInvalidValue;  // every worker must belong to a wave
     const TopkArgs ta = topk_args(P, w);
     // only the waves that own a row
-    const dim3 grid(static_cast<unsigned>(P.n_tiles * 4)), block(64 * static_cast<unsigned>((P.desc.M + R - 1) / R));
+    const dim3 grid(static_cast<unsigned>(P.n_tiles * 4)), block(64 * static_cast<unsigned>(std::min((P.desc.M + R - 1) / R, NG)));
     // Unused LDS that caps the workgroups per CU of a step that streams from
     // HBM (see fused_by_m).
     const double bytes = 16.0 * P.desc.M * static_cast<double>(P.desc.ld);
@@ -1145,10 +1153,10 @@ hipError_t split_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
     // Only 8-bit planes have a second store kind (store_fields32).
     constexpr bool kTwoKinds = (KIND == kQsgd || KIND == kMbit) && LB == 8;
     if (kTwoKinds && a.stream_msg)
-        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, kTwoKinds>), grid, block, cap, st, G, E, W, WX, Qhat, w.sign,
+        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, NB, kTwoKinds>), grid, block, cap, st, G, E, W, WX, Qhat, w.sign,
                            w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a, inv_m(P.desc.M), ta);
     else
-        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, false>), grid, block, cap, st, G, E, W, WX, Qhat, w.sign,
+        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, NB, false>), grid, block, cap, st, G, E, W, WX, Qhat, w.sign,
                            w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a, inv_m(P.desc.M), ta);
     return hipGetLastError();
 }
@@ -1172,6 +1180,7 @@ hipError_t fused_by_m(const dqgan_plan_s &P, const RowArgs &a, const float *G, f
     if (M <= 32) return split_launch<KIND, LB, 4, 8>(P, a, G, E, W, WX, w, Qhat, st);
     if (M <= 64) return split_launch<KIND, LB, 4, 16>(P, a, G, E, W, WX, w, Qhat, st);
     if (M <= 128) return split_launch<KIND, LB, 8, 16>(P, a, G, E, W, WX, w, Qhat, st);
+    if (M <= 256) return split_launch<KIND, LB, 4, 16, 4>(P, a, G, E, W, WX, w, Qhat, st);
     return fused_launch<KIND, LB, 0>(P, a, G, E, W, WX, w, Qhat, st);
 }
 
