@@ -69,9 +69,10 @@ constexpr int kTopkTile = 256;            // elements per counting tile (one wav
 constexpr int kRowCtrWords = 64;          // words per row (one 256-byte block)
 constexpr int kCtrCand = 0, kCtrAbove = 1, kCtrSpill = 2;
 constexpr int kCtrPlay = 3;  // candidates still in play after the first key digit, listed for the finish
+constexpr int kCtrClaim = 8;      // + phase: chunks of the full-row search claimed by workgroups
+constexpr int kCtrFinished = 16;  // + phase: chunks they have finished
 constexpr int kTopkChunkTiles = 64;       // tiles per workgroup of the full pass: one candidate run each
 constexpr int kSampleBins = 32768;        // sample histogram: key >> 16 (keys < 2^31)
-constexpr int64_t kSampleStride = 65536;  // one 256-element chunk sampled per 65536 elements
 constexpr int kDigitBins = 2048;          // radix-select histograms: 11-bit digits
 constexpr int kSelectPasses = 6;          // histogram slots of a search: up to 3 key digits, 3 index digits
 
@@ -79,7 +80,8 @@ constexpr int kSelectPasses = 6;          // histogram slots of a search: up to 
 struct TopkScratch {
     TopkRow *rows = nullptr;        // [M]
     uint32_t *ctr = nullptr;        // [M][kRowCtrWords] the full pass's counters of each row, apart from rows
-    uint32_t *hist = nullptr;       // [M][kSampleBins] sample histogram (zero between iterations)
+    uint32_t *hist = nullptr;       // [M][kSampleBins] first digit of the sample (zero between iterations); holds
+                                    // ref_hist, coarse and done too
     uint32_t *sel_hist = nullptr;   // [M][kDigitBins] histogram of the first key digit among the candidates
     uint2 *play = nullptr;          // [M][cap] the candidates in play after the first key digit
     uint32_t *fb_hist = nullptr;    // [M][kSelectPasses][kDigitBins] digit histograms of the full-row search
@@ -94,7 +96,13 @@ struct TopkScratch {
     int64_t n_agg_tiles = 0;
     int64_t n_tiles = 0;
     int64_t n_chunks = 0;           // chunks of kTopkChunkTiles tiles per row
-    int64_t n_sample_chunks = 0;    // sampled chunks per row
+    int64_t sample_stride = 0;      // elements from one sampled run to the next
+    int64_t n_sample_quads = 0;     // sampled quads per row
+    uint32_t *sample_keys = nullptr;  // [M][n_sample_quads][4] the sampled keys of longer rows
+    bool row_search = false;        // one workgroup per row searches and scans (k_topk_select_row)
+    uint32_t *ref_hist = nullptr;   // [M][2][kDigitBins] second digit of the sample (zero between iterations)
+    uint32_t *coarse = nullptr;     // [M][4] first digits of the sample's band (find_bins)
+    uint32_t *done = nullptr;       // [M] sample workgroups that have arrived (zero between launches)
     uint32_t n_samples = 0;         // sampled elements per row
 };
 

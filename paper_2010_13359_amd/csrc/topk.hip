@@ -28,6 +28,8 @@
 // six digits of (key, ~index) (one read of the row per digit) and a recount.
 // The fused apply pass then writes (value, index) in ascending index order
 // from each tile's position.
+#include <algorithm>
+
 #include "device.hpp"
 #include "plan.hpp"
 
@@ -130,55 +132,6 @@ __device__ bool wave_find_desc(const uint32_t *h, int nb, uint32_t rank, uint32_
     return true;
 }
 
-// 1. Sample histogram of key >> 16 (one 256-element chunk per 65536 elements).
-// The 128 KiB LDS histogram allows one workgroup per CU, so a row has few
-// workgroups (each flushes its nonzero bins with global atomics) and each
-// of their 16 waves keeps four chunks' loads in flight.
-constexpr int kSampleThreads = 1024;
-constexpr int kSampleBlocks = 4;  // workgroups per row
-constexpr int kSampleU = 4;       // chunks in flight per wave
-
-__global__ __launch_bounds__(kSampleThreads) void k_topk_sample(const float *__restrict__ G,
-                                                                const float *__restrict__ E, float eta, int64_t d,
-                                                                int64_t ld, int64_t n_chunks,
-                                                                uint32_t *__restrict__ hist) {
-    constexpr int kWaves = kSampleThreads / 64;
-    __shared__ uint32_t h[kSampleBins];
-    const int m = blockIdx.y;
-    for (int b = threadIdx.x; b < kSampleBins; b += kSampleThreads) h[b] = 0;
-    __syncthreads();
-    const float *g = G + static_cast<int64_t>(m) * ld;
-    const float *e = E + static_cast<int64_t>(m) * ld;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kWaves;
-    for (int64_t c0 = static_cast<int64_t>(blockIdx.x) * kWaves + wave; c0 < n_chunks; c0 += stride * kSampleU) {
-        f32x4 gv[kSampleU], ev[kSampleU];
-#pragma unroll
-        for (int u = 0; u < kSampleU; ++u) {
-            // chunks past the row's last are not examined; their loads read
-            // the first chunk (always in bounds)
-            const int64_t c = c0 + stride * u;
-            const int64_t i0 = (c < n_chunks ? c * kSampleStride : 0) + 4 * lane;
-            gv[u] = ld4(g + i0);
-            ev[u] = ld4(e + i0);
-        }
-#pragma unroll
-        for (int u = 0; u < kSampleU; ++u) {
-            const int64_t c = c0 + stride * u;
-            const int64_t i0 = c * kSampleStride + 4 * lane;
-            if (c < n_chunks && i0 < d) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (i0 + k < d) atomicAdd(&h[key_of(elem(gv[u], k), elem(ev[u], k), eta) >> 16], 1u);
-            }
-        }
-    }
-    __syncthreads();
-    uint32_t *hm = hist + static_cast<int64_t>(m) * kSampleBins;
-    for (int b = threadIdx.x; b < kSampleBins; b += kSampleThreads)
-        if (h[b]) atomicAdd(&hm[b], h[b]);
-}
-
 // Exclusive prefix sum of v over the 1024 threads of a workgroup (wsum: 16
 // words of LDS); total receives the sum over all threads.
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *wsum, uint32_t &total) {
@@ -200,80 +153,310 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *w
     return wbase + incl - v;
 }
 
-// 2. Band: the sample ranks k/d * s -+ 8 sigma (binomial) bracket the k-th
-// key; the bins where the count from the top reaches them bound [lo, hi].
-__global__ __launch_bounds__(1024) void k_topk_band(uint32_t *__restrict__ hist, uint32_t *__restrict__ sel_hist,
-                                                    TopkRow *__restrict__ rows, uint32_t *__restrict__ ctr,
-                                                    uint32_t n_samples, int64_t d, int64_t k) {
-    // thread t holds the t-th group of kPer bins counted from the top; a
-    // block scan finds the group where the count from the top reaches a
-    // rank, and that thread finds the bin in its registers.
-    constexpr int kPer = kSampleBins / 1024;
-    __shared__ uint32_t wsum[16];
-    __shared__ uint32_t found[2];
-    const int m = blockIdx.x;
-    const int t = threadIdx.x;
-    const uint32_t *h = hist + static_cast<int64_t>(m) * kSampleBins;
-    uint32_t asc[kPer];  // bins kSampleBins - kPer (t+1) .. kSampleBins - kPer t - 1, ascending
-    const uint4 *src = reinterpret_cast<const uint4 *>(h + kSampleBins - kPer * (t + 1));
-#pragma unroll
-    for (int q = 0; q < kPer / 4; ++q) {
-        const uint4 v = src[q];
-        asc[4 * q] = v.x;
-        asc[4 * q + 1] = v.y;
-        asc[4 * q + 2] = v.z;
-        asc[4 * q + 3] = v.w;
-    }
-    // the histogram is zeroed once read (the next iteration's sample starts
-    // from zero), and so are the row's candidate digit histograms
-    uint4 *dst = reinterpret_cast<uint4 *>(hist + static_cast<int64_t>(m) * kSampleBins + kSampleBins - kPer * (t + 1));
-#pragma unroll
-    for (int q = 0; q < kPer / 4; ++q) dst[q] = make_uint4(0u, 0u, 0u, 0u);
-    for (int b = t; b < kDigitBins; b += 1024) sel_hist[static_cast<int64_t>(m) * kDigitBins + b] = 0u;
-    uint32_t s = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) s += asc[j];
-    if (t == 0) found[0] = found[1] = 0xFFFFFFFFu;
-    uint32_t total;
-    const uint32_t excl = block_exclusive_scan(s, wsum, total);  // count above this group
-    const double f = static_cast<double>(k) / static_cast<double>(d);
-    const double ns = static_cast<double>(n_samples);
+// 1. and 2. Sample and band.  A row's sample is one run of 64 elements every
+// `stride` elements; the sample ranks k/d * s -+ 8 sigma (binomial) bracket
+// the k-th key, and the sample keys at these ranks, found to 15 + 11 bits, are
+// the band [lo, hi].  Short runs: a run wholly inside a layer of large
+// gradients counts as one draw, not as many, so the spread grows with the run
+// (with runs of 256, 6 % of the layouts and sizes tried lay beyond 8 sigma,
+// with runs of 64 none beyond 4.4).  Not single lines: what a run costs is its
+// page's translation (runs of 32 over 16 rows of 10^8: 0.7 TB/s).  Two digits:
+// once error feedback has piled the entries up under the threshold, a 15-bit
+// digit alone (0.8 % of the key's value) holds more than k of them.
+constexpr int kSampleRun = 64;  // elements
+constexpr int kSampleThreads = 1024;
+constexpr int kSampleU = 4;  // quads (g and e) in flight per thread
+
+// LDS place of bin b: the bins of one thread's group (32 consecutive) fall
+// into different banks from its neighbours'.
+__device__ __forceinline__ int bin_at(int b) { return b ^ ((b >> 5) & 31); }
+
+struct SampleArgs {
+    float eta;
+    int64_t d, ld, k;
+    int64_t n_quads;   // sampled quads per row
+    int64_t stride;    // elements from run to run
+    uint32_t n_samples;
+};
+
+// The sampled quad n of a row: its first element.
+__device__ __forceinline__ int64_t sample_i0(const SampleArgs &a, int64_t n) {
+    return (n / (kSampleRun / 4)) * a.stride + 4 * (n % (kSampleRun / 4));
+}
+
+// The sample ranks (from the top; 0: open) whose keys bound the band: [0] the
+// upper, [1] the lower.
+__device__ __forceinline__ void band_ranks(const SampleArgs &a, uint32_t (&want)[2]) {
+    const double f = static_cast<double>(a.k) / static_cast<double>(a.d);
+    const double ns = static_cast<double>(a.n_samples);
     const double mean = f * ns;
     const double sd = sqrt(ns * f * (1.0 - f)) + 1.0;
     const double z = 8.0;
-    const double a = floor(mean - z * sd);
-    const double c = ceil(mean + z * sd);
-    // ranks (from the top) whose bins bound the band: a + 1 for hi, c for lo
-    const uint32_t want[2] = {a >= 1.0 ? static_cast<uint32_t>(a) + 1u : 0u,
-                              c <= ns ? static_cast<uint32_t>(c) : 0u};
+    const double lo = floor(mean - z * sd);
+    const double hi = ceil(mean + z * sd);
+    want[0] = lo >= 1.0 ? static_cast<uint32_t>(lo) + 1u : 0u;
+    want[1] = hi <= ns ? static_cast<uint32_t>(hi) : 0u;
+}
+
+// Finds the bins of both ranks among the counts of a workgroup's threads:
+// thread t holds the bins kSampleBins - 32 (t + 1) .. - 32 t - 1, ascending,
+// in asc.  res[r]: the bin (0xFFFFFFFF: open), res[2 + r]: the rank within it.
+__device__ __forceinline__ void find_bins(const uint32_t (&asc)[32], const uint32_t (&want)[2], uint32_t *wsum,
+                                          uint32_t *res) {
+    uint32_t s = 0;
+#pragma unroll
+    for (int j = 0; j < 32; ++j) s += asc[j];
+    if (threadIdx.x < 2) res[threadIdx.x] = 0xFFFFFFFFu;
+    uint32_t total;
+    const uint32_t excl = block_exclusive_scan(s, wsum, total);  // count above this thread's bins
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const uint32_t rank = want[r];
         if (rank != 0u && excl < rank && rank <= excl + s) {
             uint32_t acc = excl;
-            for (int j = 0; j < kPer; ++j) {
-                const uint32_t cnt = asc[kPer - 1 - j];
-                if (acc + cnt >= rank) {
-                    found[r] = static_cast<uint32_t>(kSampleBins - 1 - (kPer * t + j));
-                    break;
+            bool found = false;
+#pragma unroll
+            for (int j = 0; j < 32; ++j) {
+                const uint32_t cnt = asc[31 - j];
+                if (!found && acc + cnt >= rank) {
+                    res[r] = static_cast<uint32_t>(kSampleBins - 1 - (32 * static_cast<int>(threadIdx.x) + j));
+                    res[2 + r] = rank - acc;
+                    found = true;
                 }
                 acc += cnt;
             }
         }
     }
     __syncthreads();
-    if (t == 0) {
-        uint32_t hi = 0x7FFFFFFFu, lo = 0u;
-        if (found[0] != 0xFFFFFFFFu) hi = ((found[0] + 1u) << 16) - 1u;
-        if (found[1] != 0xFFFFFFFFu) lo = found[1] << 16;
-        if (lo > hi) lo = 0u;
-        TopkRow row{};
-        row.lo = lo;
-        row.hi = hi;
-        rows[m] = row;
-        uint32_t *c = ctr + static_cast<int64_t>(m) * kRowCtrWords;
-        c[kCtrCand] = c[kCtrAbove] = c[kCtrSpill] = c[kCtrPlay] = 0u;
+}
+
+// The band from the second digits: wave r finds the place of rank res[2 + r]
+// in the histogram sub + r kDigitBins of (key >> 5) & 0x7FF among the keys of
+// bin res[r]; the row's record and counters are then set for the pass.
+__device__ __forceinline__ void write_band(const uint32_t *sub, const uint32_t *res, uint32_t *edge,
+                                           TopkRow *__restrict__ row, uint32_t *__restrict__ ctr) {
+    const int wave = threadIdx.x >> 6;
+    if (wave < 2) {
+        uint32_t e = wave == 0 ? 0x7FFFFFFFu : 0u;
+        if (res[wave] != 0xFFFFFFFFu) {
+            uint32_t bin = 0, above = 0;
+            wave_find_desc(sub + wave * kDigitBins, kDigitBins, res[2 + wave], bin, above);
+            e = (res[wave] << 16) | (bin << 5) | (wave == 0 ? 31u : 0u);
+        }
+        if ((threadIdx.x & 63) == 0) edge[wave] = e;
     }
+    __syncthreads();
+    if (threadIdx.x < kRowCtrWords) ctr[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) {
+        TopkRow r{};
+        r.hi = edge[0];
+        r.lo = edge[1] <= edge[0] ? edge[1] : 0u;
+        *row = r;
+    }
+}
+
+// Whether this workgroup is the last of n to arrive at *done; everything the
+// others wrote before arriving is then visible to it.  Called by every thread.
+// One thread's fences stand for the workgroup (the barriers order the other
+// threads' accesses before and after them): an agent-scope release writes the
+// whole L2 back, and one per wave made the sample 125 and the band 82 us over
+// 16 rows of 10^8.
+__device__ __forceinline__ bool last_to_arrive(uint32_t *done, uint32_t n, uint32_t *flag) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        const bool last = atomicAdd(done, 1u) == n - 1u;
+        __threadfence();
+        *flag = last ? 1u : 0u;
+    }
+    __syncthreads();
+    return *flag != 0u;
+}
+
+// Rows of at most kSampleThreads * 32 sampled elements: one workgroup per row
+// holds them in registers and finds both digits.  (8 rows of 10^6: 19 us for
+// the sample, band and their launches before.)
+constexpr int kRowQuads = 8;  // quads per thread
+
+__global__ __launch_bounds__(kSampleThreads) void k_topk_band_row(const float *__restrict__ G,
+                                                                  const float *__restrict__ E, SampleArgs a,
+                                                                  uint32_t *__restrict__ sel_hist,
+                                                                  TopkRow *__restrict__ rows,
+                                                                  uint32_t *__restrict__ ctr) {
+    __shared__ uint32_t h[kSampleBins];
+    __shared__ uint32_t wsum[16], res[4], edge[2];
+    const int m = blockIdx.x;
+    const int t = threadIdx.x;
+    const float *g = G + static_cast<int64_t>(m) * a.ld;
+    const float *e = E + static_cast<int64_t>(m) * a.ld;
+    uint32_t key[kRowQuads][4];  // 0xFFFFFFFF: no element
+#pragma unroll
+    for (int u0 = 0; u0 < kRowQuads; u0 += kSampleU) {
+        f32x4 gv[kSampleU], ev[kSampleU];
+#pragma unroll
+        for (int u = 0; u < kSampleU; ++u) {
+            const int64_t n = t + static_cast<int64_t>(kSampleThreads) * (u0 + u);
+            const int64_t i0 = n < a.n_quads ? sample_i0(a, n) : 0;  // (a run's end past d is inside the padded row)
+            gv[u] = ld4(g + i0);
+            ev[u] = ld4(e + i0);
+        }
+        if (u0 == 0) {
+            for (int b = t; b < kSampleBins / 4; b += kSampleThreads)
+                reinterpret_cast<u32x4 *>(h)[b] = u32x4{0u, 0u, 0u, 0u};
+            for (int b = t; b < kDigitBins; b += kSampleThreads) sel_hist[static_cast<int64_t>(m) * kDigitBins + b] = 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kSampleU; ++u) {
+            const int64_t n = t + static_cast<int64_t>(kSampleThreads) * (u0 + u);
+            const int64_t i0 = sample_i0(a, n);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                key[u0 + u][c] = n < a.n_quads && i0 + c < a.d ? key_of(elem(gv[u], c), elem(ev[u], c), a.eta)
+                                                               : 0xFFFFFFFFu;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kRowQuads; ++u) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (key[u][c] != 0xFFFFFFFFu) atomicAdd(&h[bin_at(static_cast<int>(key[u][c] >> 16))], 1u);
+    }
+    __syncthreads();
+    uint32_t asc[32], want[2];
+#pragma unroll
+    for (int j = 0; j < 32; ++j) asc[j] = h[bin_at(kSampleBins - 32 * (t + 1) + j)];
+    band_ranks(a, want);
+    find_bins(asc, want, wsum, res);  // ends with a barrier: h is free
+    for (int b = t; b < 2 * kDigitBins; b += kSampleThreads) h[b] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kRowQuads; ++u) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t b = key[u][c] >> 16, l = (key[u][c] >> 5) & 0x7FFu;
+            if (key[u][c] == 0xFFFFFFFFu) continue;
+            if (b == res[0]) atomicAdd(&h[l], 1u);
+            if (b == res[1]) atomicAdd(&h[kDigitBins + l], 1u);
+        }
+    }
+    __syncthreads();
+    write_band(h, res, edge, rows + m, ctr + static_cast<int64_t>(m) * kRowCtrWords);
+}
+
+// Longer rows: several workgroups per row build each digit's histogram, and
+// the last of them to arrive finds the bins.  The 128 KiB LDS histogram of the
+// first digit allows one workgroup per CU.
+__global__ __launch_bounds__(kSampleThreads) void k_topk_sample(const float *__restrict__ G,
+                                                                const float *__restrict__ E, SampleArgs a,
+                                                                uint32_t *__restrict__ hist,
+                                                                u32x4 *__restrict__ keys,
+                                                                uint32_t *__restrict__ coarse,
+                                                                uint32_t *__restrict__ done) {
+    __shared__ uint32_t h[kSampleBins];
+    __shared__ uint32_t wsum[16], res[4], flag;
+    const int m = blockIdx.y;
+    const int t = threadIdx.x;
+    const float *g = G + static_cast<int64_t>(m) * a.ld;
+    const float *e = E + static_cast<int64_t>(m) * a.ld;
+    for (int b = t; b < kSampleBins / 4; b += kSampleThreads) reinterpret_cast<u32x4 *>(h)[b] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kSampleThreads;
+    for (int64_t n0 = static_cast<int64_t>(blockIdx.x) * kSampleThreads + t; n0 < a.n_quads; n0 += step * kSampleU) {
+        f32x4 gv[kSampleU], ev[kSampleU];
+#pragma unroll
+        for (int u = 0; u < kSampleU; ++u) {
+            const int64_t n = n0 + step * u;
+            const int64_t i0 = n < a.n_quads ? sample_i0(a, n) : 0;
+            gv[u] = ld4(g + i0);
+            ev[u] = ld4(e + i0);
+        }
+#pragma unroll
+        for (int u = 0; u < kSampleU; ++u) {
+            const int64_t n = n0 + step * u, i0 = sample_i0(a, n);
+            if (n >= a.n_quads) break;
+            uint32_t key[4];  // 0xFFFFFFFF: no element
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                key[c] = i0 + c < a.d ? key_of(elem(gv[u], c), elem(ev[u], c), a.eta) : 0xFFFFFFFFu;
+                if (i0 + c < a.d) atomicAdd(&h[bin_at(static_cast<int>(key[c] >> 16))], 1u);
+            }
+            keys[m * a.n_quads + n] = u32x4{key[0], key[1], key[2], key[3]};
+        }
+    }
+    __syncthreads();
+    uint32_t *hm = hist + static_cast<int64_t>(m) * kSampleBins;
+    for (int b = t; b < kSampleBins; b += kSampleThreads) {
+        const uint32_t n = h[bin_at(b)];
+        if (n) atomicAdd(&hm[b], n);
+    }
+    if (!last_to_arrive(done + m, gridDim.x, &flag)) return;
+    // the row's whole histogram, zeroed once read (the next iteration's sample
+    // starts from zero)
+    uint32_t asc[32], want[2];
+    uint4 *src = reinterpret_cast<uint4 *>(hm + kSampleBins - 32 * (t + 1));
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const uint4 v = src[q];
+        asc[4 * q] = v.x;
+        asc[4 * q + 1] = v.y;
+        asc[4 * q + 2] = v.z;
+        asc[4 * q + 3] = v.w;
+        src[q] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    band_ranks(a, want);
+    find_bins(asc, want, wsum, res);
+    if (t < 4) coarse[4 * m + t] = res[t];
+    if (t == 0) done[m] = 0u;
+}
+
+__global__ __launch_bounds__(kSampleThreads) void k_topk_band(SampleArgs a, const u32x4 *__restrict__ keys,
+                                                              const uint32_t *__restrict__ coarse,
+                                                              uint32_t *__restrict__ ref_hist,
+                                                              uint32_t *__restrict__ sel_hist,
+                                                              TopkRow *__restrict__ rows, uint32_t *__restrict__ ctr,
+                                                              uint32_t *__restrict__ done) {
+    __shared__ uint32_t h[2 * kDigitBins];
+    __shared__ uint32_t res[4], edge[2], flag;
+    const int m = blockIdx.y;
+    const int t = threadIdx.x;
+    for (int b = t; b < 2 * kDigitBins; b += kSampleThreads) h[b] = 0u;
+    if (t < 4) res[t] = coarse[4 * m + t];
+    __syncthreads();
+    const uint32_t b0 = res[0], b1 = res[1];
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kSampleThreads;
+    for (int64_t n0 = static_cast<int64_t>(blockIdx.x) * kSampleThreads + t; n0 < a.n_quads; n0 += step * kSampleU) {
+        u32x4 kv[kSampleU];
+#pragma unroll
+        for (int u = 0; u < kSampleU; ++u) {
+            const int64_t n = n0 + step * u;
+            kv[u] = keys[m * a.n_quads + (n < a.n_quads ? n : 0)];
+        }
+#pragma unroll
+        for (int u = 0; u < kSampleU; ++u) {
+            if (n0 + step * u >= a.n_quads) break;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t key = elem(kv[u], c), b = key >> 16, l = (key >> 5) & 0x7FFu;
+                if (key == 0xFFFFFFFFu) continue;
+                if (b == b0) atomicAdd(&h[l], 1u);
+                if (b == b1) atomicAdd(&h[kDigitBins + l], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    uint32_t *hm = ref_hist + static_cast<int64_t>(m) * 2 * kDigitBins;
+    for (int b = t; b < 2 * kDigitBins; b += kSampleThreads)
+        if (h[b]) atomicAdd(&hm[b], h[b]);
+    if (!last_to_arrive(done + m, gridDim.x, &flag)) return;
+    for (int b = t; b < 2 * kDigitBins; b += kSampleThreads) {
+        h[b] = hm[b];
+        hm[b] = 0u;
+    }
+    for (int b = t; b < kDigitBins; b += kSampleThreads) sel_hist[static_cast<int64_t>(m) * kDigitBins + b] = 0u;
+    if (t == 0) done[m] = 0u;
+    __syncthreads();
+    write_band(h, res, edge, rows + m, ctr + static_cast<int64_t>(m) * kRowCtrWords);
 }
 
 // 3. Full pass: per tile the count of keys above the band, and the in-band
@@ -294,15 +477,17 @@ __global__ __launch_bounds__(1024) void k_topk_band(uint32_t *__restrict__ hist,
 // stores them from the top of the list down ("spills").  A tile wholly below d
 // (all but the last of a row) is classified without per-element bounds
 // tests, on masks taken straight from the comparisons.
-constexpr int kPassRounds = 4;
-constexpr int kPassTilesPerWave = 4 * kPassRounds;
-constexpr int kPassTilesPerBlock = kPassTilesPerWave * (kBlock / 64);
+// ROUNDS: 4 where that leaves enough workgroups to fill the chip (64 tiles, one
+// chunk of the tile scan, per workgroup), else 1 (16 tiles).
+template <int ROUNDS>
 __global__ __launch_bounds__(kBlock) void k_topk_pass(const float *__restrict__ G, const float *__restrict__ E,
                                                       float eta, int64_t d, int64_t ld, int64_t n_tiles,
                                                       const TopkRow *__restrict__ rows, uint32_t *__restrict__ ctr,
                                                       uint16_t *__restrict__ tile_cnt, uint32_t *__restrict__ ckey,
                                                       uint32_t *__restrict__ cidx,
                                                       int64_t cap, uint2 *__restrict__ runs, int64_t n_chunks) {
+    constexpr int kPassTilesPerWave = 4 * ROUNDS;
+    constexpr int kPassTilesPerBlock = kPassTilesPerWave * (kBlock / 64);
     constexpr uint32_t kStage = 256;  // staged candidates per wave
     constexpr int kWaves = kBlock / 64;
     __shared__ uint2 buf[kWaves][kStage];
@@ -320,7 +505,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_pass(const float *__restrict__ 
     const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kPassTilesPerBlock + kPassTilesPerWave * wave;
     uint32_t my_cnt = 0;  // lane j < 16: above-band count of tile t0 + j
     uint32_t ns = 0;      // wave-uniform: candidates staged by the wave
-    for (int round = 0; round < kPassRounds; ++round) {
+    for (int round = 0; round < ROUNDS; ++round) {
         // Unconditional loads (a tile past the row's end reads the last tile
         // again and is not examined): loads under a branch made the compiler
         // wait for each tile's loads before issuing the next tile's.
@@ -401,13 +586,13 @@ __global__ __launch_bounds__(kBlock) void k_topk_pass(const float *__restrict__ 
             }
         }
     }
-    // the wave's 16 tile counts: lanes 0..15, one contiguous store
+    // the wave's tile counts: its first lanes, one contiguous store
     if (lane < kPassTilesPerWave && t0 + lane < n_tiles)
         tile_cnt[static_cast<int64_t>(m) * n_tiles + t0 + lane] = static_cast<uint16_t>(my_cnt);
-    // keys above the band in the wave's tiles: the sum of its 16 tile counts
+    // keys above the band in the wave's tiles: the sum of its tile counts
     uint32_t nab = my_cnt;
 #pragma unroll
-    for (int o = 1; o < kPassTilesPerWave; o <<= 1) nab += __shfl_xor(nab, o);
+    for (int o = 1; o < kPassTilesPerWave; o <<= 1) nab += __shfl_xor(nab, o);  // lanes 0 .. kPassTilesPerWave - 1
     if (lane == 0) {
         wave_nab[wave] = nab;
         wave_ns[wave] = ns;
@@ -423,7 +608,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_pass(const float *__restrict__ 
         uint32_t *c = ctr + static_cast<int64_t>(m) * kRowCtrWords;
         if (a) atomicAdd(c + kCtrAbove, a);
         base = n ? atomicAdd(c + kCtrCand, n) : 0u;
-        runs[static_cast<int64_t>(m) * n_chunks + blockIdx.x] = make_uint2(base, n);
+        if (runs) runs[static_cast<int64_t>(m) * n_chunks + blockIdx.x] = make_uint2(base, n);
     }
     __syncthreads();
     uint32_t off = base;
@@ -715,22 +900,15 @@ __global__ __launch_bounds__(1024) void k_topk_sel_finish(TopkRow *__restrict__ 
 }
 
 // 6. Full-row search of a row whose band missed: six digits of (key, ~index)
-// over the whole row, one histogram slot per digit.  The kernels loop over
-// the rows (a 1-D grid of kFbBlocks workgroups), so that when no row falls
-// back -- the usual case -- each launch is a short loop over the row flags.
+// over the whole row, one histogram slot per digit, then the row's tile
+// counts, in one launch that is a short read of the row flags when no row
+// fell back -- the usual case (seven launches before: 2.2 to 5 us each).
+// The workgroups claim a phase's chunks (64 tiles) from a counter and go on to
+// the next phase when the number of finished chunks is complete.  A workgroup
+// thus waits only for chunks that running workgroups have claimed, never for
+// a workgroup that has not started (one that starts late finds nothing left
+// to claim): the waits end whatever part of the grid the device runs at once.
 constexpr int kMaxRows = 1024;  // the library's largest worker count
-
-// The rows that fell back, gathered into LDS by the whole workgroup with one
-// parallel read of the flags (the order does not matter: rows are
-// independent).  Returns their number.
-__device__ int gather_fallback_rows(const TopkRow *__restrict__ rows, int M, int *fb_rows, int *n_fb) {
-    if (threadIdx.x == 0) *n_fb = 0;
-    __syncthreads();
-    for (int m = threadIdx.x; m < M; m += kBlock)
-        if (rows[m].fallback) fb_rows[atomicAdd(n_fb, 1)] = m;
-    __syncthreads();
-    return *n_fb;
-}
 
 struct FbState {
     uint32_t rank, kprefix, iprefix, T, I;
@@ -762,122 +940,350 @@ __device__ FbState fb_replay(int64_t k, const uint32_t *__restrict__ f6, int upt
     return s;
 }
 
-__global__ __launch_bounds__(kBlock) void k_topk_fb_hist(int pass, const float *__restrict__ G,
-                                                         const float *__restrict__ E, float eta, int64_t d, int64_t ld,
-                                                         int32_t M, int64_t k, const TopkRow *__restrict__ rows,
-                                                         uint32_t *__restrict__ fb_hist) {
+// Exclusive scan of one row's tile counts by a workgroup of 256 threads: the
+// tiles' offsets within their chunk of kTopkChunkTiles tiles (one chunk per
+// wave and round) and the chunks' offsets.
+__device__ void scan_tiles(const uint16_t *__restrict__ cnt, uint16_t *__restrict__ tile_off,
+                           uint32_t *__restrict__ chunk_off, int64_t n_tiles, uint32_t *__restrict__ total) {
+    constexpr int kWaves = kBlock / 64;
+    __shared__ uint32_t sums[kWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t carry = 0;
+    for (int64_t c0 = 0; c0 * kTopkChunkTiles < n_tiles; c0 += kWaves) {
+        const int64_t t = (c0 + wave) * kTopkChunkTiles + lane;
+        const uint32_t v = t < n_tiles ? cnt[t] : 0u;
+        uint32_t incl = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t x = __shfl_up(incl, o);
+            if (lane >= o) incl += x;
+        }
+        if (t < n_tiles) tile_off[t] = static_cast<uint16_t>(incl - v);
+        if (lane == 63) sums[wave] = incl;
+        __syncthreads();
+        uint32_t before = carry;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < wave) before += sums[w];
+            carry += sums[w];
+        }
+        if (lane == 0 && t < n_tiles) chunk_off[c0 + wave] = before;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *total = carry;
+}
+
+// SCAN: the tile scan of a fallen-back row too (short rows, whose other tile
+// scans the search kernel does); otherwise the spilled candidates (stored from
+// the top of the list) of the rows whose search decided are added to their
+// tiles' counts here, before the scan kernels.
+template <bool SCAN>
+__global__ __launch_bounds__(kBlock) void k_topk_fallback(const float *__restrict__ G, const float *__restrict__ E,
+                                                          float eta, int64_t d, int64_t ld, int64_t n_tiles,
+                                                          int64_t n_chunks, int32_t M, int64_t k,
+                                                          TopkRow *__restrict__ rows, uint32_t *__restrict__ ctr,
+                                                          const uint32_t *__restrict__ ckey,
+                                                          const uint32_t *__restrict__ cidx, int64_t cap,
+                                                          uint32_t *__restrict__ fb_hist,
+                                                          uint16_t *__restrict__ tile_cnt,
+                                                          uint16_t *__restrict__ tile_off,
+                                                          uint32_t *__restrict__ chunk_off) {
     __shared__ uint32_t h[kDigitBins];
     __shared__ FbState st;
-    __shared__ int fb_rows[kMaxRows];
-    __shared__ int n_fb;
-    const int nf = gather_fallback_rows(rows, M, fb_rows, &n_fb);
-    for (int q = 0; q < nf; ++q) {
-        const int m = fb_rows[q];
-        uint32_t *f6 = fb_hist + static_cast<int64_t>(m) * kSelectPasses * kDigitBins;
-        if (threadIdx.x < 64) {
-            const FbState s = fb_replay(k, f6, pass);
-            if (threadIdx.x == 0) st = s;
-        }
-        __syncthreads();
-        const FbState s = st;
-        if (s.next == pass) {
-            const int nb = bins_of(pass);
-            for (int b = threadIdx.x; b < nb; b += kBlock) h[b] = 0u;
-            __syncthreads();
-            const float *g = G + static_cast<int64_t>(m) * ld;
-            const float *e = E + static_cast<int64_t>(m) * ld;
-            const int64_t nq = (d + 3) / 4;
-            for (int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; q < nq;
-                 q += static_cast<int64_t>(gridDim.x) * kBlock) {
-                const f32x4 gv = ld4(g + 4 * q), ev = ld4(e + 4 * q);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int64_t i = 4 * q + c;
-                    if (i < d) {
-                        const uint32_t key = key_of(elem(gv, c), elem(ev, c), eta);
-                        const uint32_t ni = ~static_cast<uint32_t>(i);
-                        if (in_play(pass, key, ni, s.kprefix, s.iprefix)) atomicAdd(&h[digit_of(pass, key, ni)], 1u);
-                    }
-                }
-            }
-            __syncthreads();
-            for (int b = threadIdx.x; b < nb; b += kBlock)
-                if (h[b]) atomicAdd(&f6[pass * kDigitBins + b], h[b]);
-        }
-        __syncthreads();  // st and h are reused for the next row
-    }
-}
-
-// ... then the selection of each fallen-back row per tile (and T, I).
-__global__ __launch_bounds__(kBlock) void k_topk_fb_recount(const float *__restrict__ G, const float *__restrict__ E,
-                                                            float eta, int64_t d, int64_t ld, int64_t n_tiles,
-                                                            int32_t M, int64_t k, TopkRow *__restrict__ rows,
-                                                            const uint32_t *__restrict__ fb_hist,
-                                                            uint16_t *__restrict__ tile_cnt) {
-    __shared__ FbState st;
-    __shared__ int fb_rows[kMaxRows];
-    __shared__ int n_fb;
+    __shared__ int fb_rows[kMaxRows], sp_rows[kMaxRows];
+    __shared__ int n_fb, n_sp;
+    __shared__ uint32_t claimed, is_last;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nf = gather_fallback_rows(rows, M, fb_rows, &n_fb);
-    for (int q = 0; q < nf; ++q) {
-        const int m = fb_rows[q];
-        if (threadIdx.x < 64) {
-            const FbState s = fb_replay(k, fb_hist + static_cast<int64_t>(m) * kSelectPasses * kDigitBins,
-                                        kSelectPasses);
-            if (threadIdx.x == 0) st = s;
+    if (threadIdx.x == 0) n_fb = n_sp = 0;
+    __syncthreads();
+    // the rows are looked at in parallel; those that fell back are then taken
+    // in ascending order, the same in every workgroup
+    for (int m = threadIdx.x; m < M; m += kBlock) {
+        const uint32_t fb = rows[m].fallback, ns = rows[m].n_spill;
+        fb_rows[m] = fb ? 1 : 0;
+        if (fb) atomicAdd(&n_fb, 1);
+        if (!SCAN && !fb && ns) sp_rows[atomicAdd(&n_sp, 1)] = m;
+    }
+    __syncthreads();
+    for (int q = 0; q < n_sp; ++q) {
+        const int m = sp_rows[q];
+        const uint32_t T = rows[m].T, I = rows[m].I;
+        const int64_t n = rows[m].n_spill;  // at most cap - n_cand (the search decided)
+        const uint32_t *krow = ckey + static_cast<int64_t>(m) * cap;
+        const uint32_t *irow = cidx + static_cast<int64_t>(m) * cap;
+        // 32-bit atomics on the word holding the tile's 16-bit count (n_tiles is
+        // a multiple of 4, so a row's counts start on a word; a count stays at
+        // most 256 and never carries into its neighbour)
+        uint32_t *trow = reinterpret_cast<uint32_t *>(tile_cnt + static_cast<int64_t>(m) * n_tiles);
+        for (int64_t j = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; j < n;
+             j += static_cast<int64_t>(gridDim.x) * kBlock) {
+            const uint32_t key = krow[cap - 1 - j], i = irow[cap - 1 - j];
+            if (key > T || (key == T && i <= I)) {
+                const uint32_t tile = i / kTopkTile;
+                atomicAdd(&trow[tile >> 1], 1u << (16u * (tile & 1u)));
+            }
         }
-        __syncthreads();
-        const FbState s = st;
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            rows[m].T = s.T;
-            rows[m].I = s.I;
-        }
+    }
+    if (n_fb == 0) return;
+    for (int m = 0; m < M; ++m) {
+        if (!fb_rows[m]) continue;
+        uint32_t *f6 = fb_hist + static_cast<int64_t>(m) * kSelectPasses * kDigitBins;
+        uint32_t *c = ctr + static_cast<int64_t>(m) * kRowCtrWords;
         const float *g = G + static_cast<int64_t>(m) * ld;
         const float *e = E + static_cast<int64_t>(m) * ld;
-        for (int64_t tile = static_cast<int64_t>(blockIdx.x) * 4 + wave; tile < n_tiles;
-             tile += static_cast<int64_t>(gridDim.x) * 4) {
-            const int64_t i0 = tile * kTopkTile + 4 * lane;
-            const f32x4 gv = ld4(g + i0), ev = ld4(e + i0);
-            uint32_t n = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int64_t i = i0 + c;
-                const uint32_t key = key_of(elem(gv, c), elem(ev, c), eta);
-                const bool sel = i < d && (key > s.T || (key == s.T && static_cast<uint32_t>(i) <= s.I));
-                n += __popcll(__ballot(sel));
+        // phases 0 .. 5: the digits; 6: the tile counts
+        for (int pass = 0; pass <= kSelectPasses; ++pass) {
+            if (threadIdx.x < 64) {
+                const FbState s = fb_replay(k, f6, pass);
+                if (threadIdx.x == 0) st = s;
             }
-            if (lane == 0) tile_cnt[static_cast<int64_t>(m) * n_tiles + tile] = static_cast<uint16_t>(n);
+            __syncthreads();
+            const FbState s = st;
+            const bool recount = pass == kSelectPasses;
+            if (!recount && s.next != pass) {  // decided without this digit, for every workgroup alike
+                __syncthreads();               // st is rewritten
+                continue;
+            }
+            const int nb = recount ? 0 : bins_of(pass);
+            for (int b = threadIdx.x; b < nb; b += kBlock) h[b] = 0u;
+            uint32_t mine = 0;  // chunks this workgroup took
+            for (;;) {
+                __syncthreads();
+                if (threadIdx.x == 0) claimed = atomicAdd(c + kCtrClaim + pass, 1u);
+                __syncthreads();
+                if (claimed >= n_chunks) break;
+                ++mine;
+                for (int w = wave; w < kTopkChunkTiles; w += kBlock / 64) {
+                    const int64_t tile = static_cast<int64_t>(claimed) * kTopkChunkTiles + w;
+                    if (tile >= n_tiles) break;  // whole waves
+                    const int64_t i0 = tile * kTopkTile + 4 * lane;
+                    const f32x4 gv = ld4(g + i0), ev = ld4(e + i0);
+                    uint32_t n = 0;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int64_t i = i0 + q;
+                        const uint32_t key = key_of(elem(gv, q), elem(ev, q), eta);
+                        const uint32_t ni = ~static_cast<uint32_t>(i);
+                        if (recount)
+                            n += __popcll(__ballot(i < d && (key > s.T || (key == s.T && static_cast<uint32_t>(i) <= s.I))));
+                        else if (i < d && in_play(pass, key, ni, s.kprefix, s.iprefix))
+                            atomicAdd(&h[digit_of(pass, key, ni)], 1u);
+                    }
+                    if (recount && lane == 0)
+                        tile_cnt[static_cast<int64_t>(m) * n_tiles + tile] = static_cast<uint16_t>(n);
+                }
+            }
+            if (mine) {
+                for (int b = threadIdx.x; b < nb; b += kBlock)
+                    if (h[b]) atomicAdd(&f6[pass * kDigitBins + b], h[b]);
+            }
+            // this workgroup's chunks are finished: its results first, then
+            // the count (one thread's fences, as in last_to_arrive)
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                __threadfence();
+                const uint32_t before = mine ? atomicAdd(c + kCtrFinished + pass, mine) : 0u;
+                is_last = mine && before + mine == n_chunks ? 1u : 0u;
+                if (!recount)
+                    while (__hip_atomic_load(c + kCtrFinished + pass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                           n_chunks)
+                        __builtin_amdgcn_s_sleep(8);
+                __threadfence();
+            }
+            __syncthreads();
+            if (recount && is_last) {
+                // the workgroup that finished the last chunk
+                if (threadIdx.x == 0) {
+                    rows[m].T = s.T;
+                    rows[m].I = s.I;
+                }
+                if (SCAN)
+                    scan_tiles(tile_cnt + static_cast<int64_t>(m) * n_tiles, tile_off + static_cast<int64_t>(m) * n_tiles,
+                               chunk_off + static_cast<int64_t>(m) * n_chunks, n_tiles, &rows[m].total);
+            }
+            __syncthreads();  // st, h and is_last are reused
         }
-        __syncthreads();  // st is reused for the next row
     }
 }
 
-// Spilled candidates (stored from the top of the list) added to their tiles'
-// counts, for rows whose candidate search decided; nothing to do for most
-// rows (a short exit).
-constexpr int kSpillBlocks = 16;  // workgroups per row
+// Short rows (at most kRowTiles tiles): the whole search, the tile counts and
+// their scan by one workgroup per row, which keeps the digits' histogram, the
+// candidates in play and the tile counts in LDS -- one launch for what takes
+// six on longer rows (8 rows of 10^6, k = 1 %: 58 us in six launches, see the
+// rule in launch_topk_select).  A row whose candidates do not hold the k-th
+// key is left to the full-row search.
+constexpr int kRowTiles = 8192;
+constexpr int kRowList = 4096;  // candidates in play listed in LDS; more go to the row's global list
 
-__global__ __launch_bounds__(kBlock) void k_topk_spill_count(const TopkRow *__restrict__ rows,
-                                                             const uint32_t *__restrict__ ckey,
-                                                             const uint32_t *__restrict__ cidx, int64_t cap,
-                                                             uint16_t *__restrict__ tile_cnt, int64_t n_tiles) {
-    const int m = blockIdx.y;
-    const TopkRow r = rows[m];
-    if (r.fallback || r.n_spill == 0) return;
+__global__ __launch_bounds__(1024) void k_topk_select_row(TopkRow *__restrict__ rows, uint32_t *__restrict__ ctr,
+                                                          const uint32_t *__restrict__ ckey,
+                                                          const uint32_t *__restrict__ cidx, int64_t cap, int64_t k,
+                                                          uint2 *__restrict__ play, uint32_t *__restrict__ fb_hist,
+                                                          const uint16_t *__restrict__ tile_cnt,
+                                                          uint16_t *__restrict__ tile_off,
+                                                          uint32_t *__restrict__ chunk_off, int64_t n_tiles,
+                                                          int64_t n_chunks) {
+    constexpr int kThreads = 1024, kPer = kRowTiles / kThreads;
+    __shared__ uint32_t h[kDigitBins];
+    __shared__ uint2 list[kRowList];
+    __shared__ uint32_t cnt[kRowTiles / 2];  // two tiles' 16-bit counts per word (at most 256 each)
+    __shared__ uint32_t wsum[16], res[3], n_list;
+    __shared__ TopState st;
+    const int m = blockIdx.x;
+    const int t = threadIdx.x;
+    TopkRow r = rows[m];
+    uint32_t *c = ctr + static_cast<int64_t>(m) * kRowCtrWords;
+    r.n_cand = c[kCtrCand];
+    r.n_above = c[kCtrAbove];
+    r.n_spill = c[kCtrSpill];
+    if (!sel_ok(r, k, cap)) {
+        uint32_t *f6 = fb_hist + static_cast<int64_t>(m) * kSelectPasses * kDigitBins;
+        for (int b = t; b < kSelectPasses * kDigitBins; b += kThreads) f6[b] = 0u;
+        if (t == 0) rows[m].fallback = 1u;
+        return;
+    }
+    const uint32_t *tc = reinterpret_cast<const uint32_t *>(tile_cnt + static_cast<int64_t>(m) * n_tiles);
+    for (int w = t; w < kRowTiles / 2; w += kThreads) cnt[w] = 2 * w < n_tiles ? tc[w] : 0u;  // n_tiles is even
     const uint32_t *krow = ckey + static_cast<int64_t>(m) * cap;
     const uint32_t *irow = cidx + static_cast<int64_t>(m) * cap;
-    // 32-bit atomics on the word holding the tile's 16-bit count (n_tiles is
-    // a multiple of 4, so a row's counts start on a word; a count stays at
-    // most 256 and never carries into its neighbour)
-    uint32_t *trow = reinterpret_cast<uint32_t *>(tile_cnt + static_cast<int64_t>(m) * n_tiles);
-    const int64_t n = r.n_spill;  // at most cap - n_cand (the search decided)
-    for (int64_t j = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; j < n;
-         j += static_cast<int64_t>(gridDim.x) * kBlock) {
-        const uint2 c = make_uint2(krow[cap - 1 - j], irow[cap - 1 - j]);
-        if (c.x > r.T || (c.x == r.T && c.y <= r.I)) {
-            const uint32_t tile = c.y / kTopkTile;
-            atomicAdd(&trow[tile >> 1], 1u << (16u * (tile & 1u)));
+    const uint32_t n = static_cast<uint32_t>(n_listed(r));
+    const int width = key_width(r);
+    // the first digit over all candidates
+    {
+        const int wbits = width < 11 ? width : 11, shift = width - wbits, nb = 1 << wbits;
+        for (int b = t; b < nb; b += kThreads) h[b] = 0u;
+        if (t == 0) n_list = 0u;
+        __syncthreads();
+        for (uint32_t j0 = t; j0 < n; j0 += kThreads * kSelU) {
+            uint32_t ks[kSelU];
+#pragma unroll
+            for (int u = 0; u < kSelU; ++u) {
+                const uint32_t j = j0 + kThreads * u;
+                ks[u] = j < n ? krow[cand_pos(j, r.n_cand, cap)] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < kSelU; ++u)
+                if (j0 + kThreads * u < n) atomicAdd(&h[(ks[u] - r.lo) >> shift], 1u);
         }
+        __syncthreads();
+        if (t < 64) {
+            const TopState s = sel_first_digit(r, k, h);
+            if (t == 0) st = s;
+        }
+        __syncthreads();
+    }
+    uint32_t rank = st.rank, kp = st.kp;
+    int top = st.top;
+    // the candidates in its bin listed, those above it counted in their tiles
+    uint2 *prow = play + static_cast<int64_t>(m) * cap;
+    for (uint32_t j0 = t; j0 < n; j0 += kThreads * kSelU) {
+        uint32_t ks[kSelU], is[kSelU];
+#pragma unroll
+        for (int u = 0; u < kSelU; ++u) {
+            const uint32_t j = j0 + kThreads * u;
+            const uint64_t p = j < n ? cand_pos(j, r.n_cand, cap) : 0;
+            ks[u] = krow[p];
+            is[u] = irow[p];
+        }
+#pragma unroll
+        for (int u = 0; u < kSelU; ++u) {
+            if (j0 + kThreads * u >= n) continue;
+            const uint32_t x = top >= 32 ? 0u : (ks[u] - r.lo) >> top, y = top >= 32 ? 0u : kp >> top;
+            if (x > y) {
+                const uint32_t tile = is[u] / kTopkTile;
+                atomicAdd(&cnt[tile >> 1], 1u << (16u * (tile & 1u)));
+            } else if (x == y) {
+                const uint32_t at = atomicAdd(&n_list, 1u);
+                if (at < kRowList) list[at] = make_uint2(ks[u], is[u]);
+                prow[at] = make_uint2(ks[u], is[u]);
+            }
+        }
+    }
+    __syncthreads();
+    const uint32_t nl = n_list;
+    const bool in_lds = nl <= kRowList;
+    auto at = [&](uint32_t j) { return in_lds ? list[j] : prow[j]; };
+    uint32_t n_bin = nl;
+    // the remaining digits of key - lo
+    while (top > 0) {
+        const int wbits = top < 11 ? top : 11;
+        const int shift = top - wbits;
+        const int nb = 1 << wbits;
+        for (int b = t; b < nb; b += kThreads) h[b] = 0u;
+        __syncthreads();
+        for (uint32_t j = t; j < nl; j += kThreads) {
+            const uint32_t rel = at(j).x - r.lo;
+            if (top >= 32 || (rel >> top) == (kp >> top)) atomicAdd(&h[(rel >> shift) & (nb - 1)], 1u);
+        }
+        __syncthreads();
+        block_find(h, nb, rank, res);
+        rank -= res[1];
+        kp |= res[0] << shift;
+        n_bin = res[2];
+        top = shift;
+        __syncthreads();
+    }
+    const uint32_t T = r.lo + kp;
+    uint32_t I = 0xFFFFFFFFu;
+    if (rank != n_bin) {
+        // the k-th key is shared and not all of its candidates are taken:
+        // three digits of ~index among them (smaller index first)
+        uint32_t ip = 0u;
+        for (int pass = 3; pass < 6; ++pass) {
+            const int nb = bins_of(pass);
+            for (int b = t; b < nb; b += kThreads) h[b] = 0u;
+            __syncthreads();
+            for (uint32_t j = t; j < nl; j += kThreads) {
+                const uint2 q = at(j);
+                if (in_play(pass, q.x, ~q.y, T, ip)) atomicAdd(&h[digit_of(pass, q.x, ~q.y)], 1u);
+            }
+            __syncthreads();
+            block_find(h, nb, rank, res);
+            uint32_t kd = 0;
+            rank -= res[1];
+            add_prefix(pass, res[0], kd, ip);
+            __syncthreads();
+        }
+        I = ~ip;
+    }
+    for (uint32_t j = t; j < nl; j += kThreads) {
+        const uint2 q = at(j);
+        if (q.x > T || (q.x == T && q.y <= I)) {
+            const uint32_t tile = q.y / kTopkTile;
+            atomicAdd(&cnt[tile >> 1], 1u << (16u * (tile & 1u)));
+        }
+    }
+    __syncthreads();
+    // the tiles' offsets within their chunk and the chunks' offsets: thread t
+    // takes tiles kPer t .. kPer t + kPer - 1, a chunk is 8 threads
+    uint32_t v[kPer], s = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; i += 2) {
+        const uint32_t w = cnt[(kPer * t + i) >> 1];
+        v[i] = w & 0xFFFFu;
+        v[i + 1] = w >> 16;
+        s += v[i] + v[i + 1];
+    }
+    uint32_t total;
+    const uint32_t excl = block_exclusive_scan(s, wsum, total);
+    constexpr int kGroup = kTopkChunkTiles / kPer;
+    const uint32_t chunk = __shfl(excl, (t & 63) & ~(kGroup - 1));
+    if (kPer * t < n_tiles) {
+        uint32_t o = excl - chunk;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (kPer * t + i < n_tiles) tile_off[static_cast<int64_t>(m) * n_tiles + kPer * t + i] = static_cast<uint16_t>(o);
+            o += v[i];
+        }
+        if (t % kGroup == 0) chunk_off[static_cast<int64_t>(m) * n_chunks + t / kGroup] = chunk;
+    }
+    if (t == 0) {
+        rows[m].n_cand = r.n_cand;
+        rows[m].n_above = r.n_above;
+        rows[m].n_spill = r.n_spill;
+        rows[m].T = T;
+        rows[m].I = I;
+        rows[m].total = total;
     }
 }
 
@@ -1497,22 +1903,35 @@ hipError_t topk_alloc(dqgan_plan_s &P) {
     const dqgan_desc &D = P.desc;
     S.n_tiles = D.ld / kTopkTile;
     S.n_chunks = (S.n_tiles + kTopkChunkTiles - 1) / kTopkChunkTiles;
-    S.n_sample_chunks = (D.d + kSampleStride - 1) / kSampleStride;
-    int64_t ns = 0;
-    for (int64_t c = 0; c < S.n_sample_chunks; ++c) {
-        const int64_t a = c * kSampleStride;
-        ns += (D.d - a < kTopkTile) ? D.d - a : kTopkTile;
-    }
-    S.n_samples = static_cast<uint32_t>(ns);
+    // The sample: as many runs as one workgroup holds for the rows it serves
+    // alone (but one in 512 elements at most), else 4096 (one in 2048 at most).
+    S.row_search = S.n_tiles <= kRowTiles;
+    const int64_t most = S.row_search ? kSampleThreads * kRowQuads * 4 / kSampleRun : 4096;
+    S.sample_stride = std::max<int64_t>(S.row_search ? 512 : 2048,
+                                        ((D.d + most - 1) / most + kSampleRun - 1) / kSampleRun * kSampleRun);
+    const int64_t runs = (D.d + S.sample_stride - 1) / S.sample_stride;
+    S.n_sample_quads = runs * (kSampleRun / 4);
+    const int64_t last = D.d - (runs - 1) * S.sample_stride;  // elements from the last run's first on
+    S.n_samples = static_cast<uint32_t>((runs - 1) * kSampleRun + std::min<int64_t>(last, kSampleRun));
     int64_t cap = D.k > 65536 ? D.k : 65536;
     S.cap = cap < D.d ? cap : D.d;
     const size_t M = static_cast<size_t>(D.M);
     const size_t digit_words = M * kSelectPasses * kDigitBins;
     hipError_t e = hipMalloc(reinterpret_cast<void **>(&S.rows), M * sizeof(TopkRow));
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&S.ctr), M * kRowCtrWords * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&S.hist), M * kSampleBins * sizeof(uint32_t));
-    // the sample histogram starts at zero; every iteration zeroes it again once read
-    if (e == hipSuccess) e = hipMemset(S.hist, 0, M * kSampleBins * sizeof(uint32_t));
+    // the sample's histograms, arrival counter and first digits (longer rows);
+    // histograms and counter start at zero, every iteration zeroes them again
+    // once read
+    const size_t sample_words = S.row_search ? 0 : M * (kSampleBins + 2 * kDigitBins + 1 + 4);
+    if (e == hipSuccess && !S.row_search)
+        e = hipMalloc(reinterpret_cast<void **>(&S.sample_keys), M * static_cast<size_t>(S.n_sample_quads) * 16);
+    if (e == hipSuccess && sample_words) {
+        e = hipMalloc(reinterpret_cast<void **>(&S.hist), sample_words * sizeof(uint32_t));
+        if (e == hipSuccess) e = hipMemset(S.hist, 0, sample_words * sizeof(uint32_t));
+        S.ref_hist = S.hist + M * kSampleBins;
+        S.coarse = S.ref_hist + M * 2 * kDigitBins;
+        S.done = S.coarse + M * 4;
+    }
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&S.sel_hist), M * kDigitBins * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&S.fb_hist), digit_words * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&S.cand), M * static_cast<size_t>(S.cap) * sizeof(uint2));
@@ -1541,6 +1960,7 @@ void topk_free(dqgan_plan_s &P) {
     (void)hipFree(S.rows);
     (void)hipFree(S.ctr);
     (void)hipFree(S.hist);
+    (void)hipFree(S.sample_keys);
     (void)hipFree(S.sel_hist);
     (void)hipFree(S.fb_hist);
     (void)hipFree(S.cand);
@@ -1561,27 +1981,42 @@ hipError_t launch_topk_select(const dqgan_plan_s &P, float eta, const float *G, 
     // the candidate lists: a key plane [M][cap], then an index plane [M][cap]
     uint32_t *ckey = reinterpret_cast<uint32_t *>(S.cand);
     uint32_t *cidx = ckey + static_cast<int64_t>(D.M) * S.cap;
-    const int64_t sb = (S.n_sample_chunks + kSampleThreads / 64 - 1) / (kSampleThreads / 64);
-    hipLaunchKernelGGL(k_topk_sample, dim3(static_cast<unsigned>(sb < kSampleBlocks ? sb : kSampleBlocks), M),
-                       dim3(kSampleThreads), 0, st,
-                       G, E, eta, D.d, D.ld, S.n_sample_chunks, S.hist);
-    hipLaunchKernelGGL(k_topk_band, dim3(M), dim3(1024), 0, st, S.hist, S.sel_hist, S.rows, S.ctr, S.n_samples, D.d,
-                       D.k);
-    hipLaunchKernelGGL(k_topk_pass, dim3(static_cast<unsigned>(S.n_chunks), M), dim3(kBlock), 0, st, G, E, eta, D.d,
-                       D.ld, S.n_tiles, S.rows, S.ctr, S.tile_cnt, ckey, cidx, S.cap, S.runs, S.n_chunks);
+    const SampleArgs sa{eta, D.d, D.ld, D.k, S.n_sample_quads, S.sample_stride, S.n_samples};
+    if (S.row_search) {
+        hipLaunchKernelGGL(k_topk_band_row, dim3(M), dim3(kSampleThreads), 0, st, G, E, sa, S.sel_hist, S.rows, S.ctr);
+    } else {
+        // one workgroup per CU; each takes at least kSampleU quads per thread
+        const int64_t most = (S.n_sample_quads + kSampleThreads * kSampleU - 1) / (kSampleThreads * kSampleU);
+        const unsigned nw = static_cast<unsigned>(std::min<int64_t>(most, std::max<int64_t>(256 / D.M, 1)));
+        hipLaunchKernelGGL(k_topk_sample, dim3(nw, M), dim3(kSampleThreads), 0, st, G, E, sa, S.hist,
+                           reinterpret_cast<u32x4 *>(S.sample_keys), S.coarse, S.done);
+        hipLaunchKernelGGL(k_topk_band, dim3(nw, M), dim3(kSampleThreads), 0, st, sa,
+                           reinterpret_cast<const u32x4 *>(S.sample_keys), S.coarse, S.ref_hist, S.sel_hist,
+                           S.rows, S.ctr, S.done);
+    }
+    if (S.row_search) {
+        // 16 tiles per workgroup: four times the workgroups
+        const unsigned nb = static_cast<unsigned>((S.n_tiles + 15) / 16);
+        hipLaunchKernelGGL((k_topk_pass<1>), dim3(nb, M), dim3(kBlock), 0, st, G, E, eta, D.d, D.ld, S.n_tiles, S.rows,
+                           S.ctr, S.tile_cnt, ckey, cidx, S.cap, static_cast<uint2 *>(nullptr), S.n_chunks);
+        hipLaunchKernelGGL(k_topk_select_row, dim3(M), dim3(1024), 0, st, S.rows, S.ctr, ckey, cidx, S.cap, D.k, S.play,
+                           S.fb_hist, S.tile_cnt, S.tile_off, S.chunk_off, S.n_tiles, S.n_chunks);
+        hipLaunchKernelGGL((k_topk_fallback<true>), dim3(kFbBlocks), dim3(kBlock), 0, st, G, E, eta, D.d, D.ld,
+                           S.n_tiles, S.n_chunks, D.M, D.k, S.rows, S.ctr, ckey, cidx, S.cap, S.fb_hist, S.tile_cnt,
+                           S.tile_off, S.chunk_off);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((k_topk_pass<4>), dim3(static_cast<unsigned>(S.n_chunks), M), dim3(kBlock), 0, st, G, E, eta,
+                       D.d, D.ld, S.n_tiles, S.rows, S.ctr, S.tile_cnt, ckey, cidx, S.cap, S.runs, S.n_chunks);
     hipLaunchKernelGGL(k_topk_sel_top, dim3(kSelBlocks, M), dim3(kBlock), 0, st, S.rows, S.ctr, ckey, S.cap, D.k,
                        S.sel_hist);
     hipLaunchKernelGGL(k_topk_sel_collect, dim3(kSelBlocks, M), dim3(kBlock), 0, st, S.rows, S.ctr, ckey, cidx,
                        S.cap, D.k, S.sel_hist, S.play);
     hipLaunchKernelGGL(k_topk_sel_finish, dim3(M), dim3(1024), 0, st, S.rows, S.ctr, S.cap, D.k, S.sel_hist, S.play,
                        S.fb_hist);
-    for (int pass = 0; pass < kSelectPasses; ++pass)
-        hipLaunchKernelGGL(k_topk_fb_hist, dim3(kFbBlocks), dim3(kBlock), 0, st, pass, G, E, eta, D.d, D.ld, D.M, D.k,
-                           S.rows, S.fb_hist);
-    hipLaunchKernelGGL(k_topk_fb_recount, dim3(256), dim3(kBlock), 0, st, G, E, eta, D.d, D.ld, S.n_tiles, D.M, D.k,
-                       S.rows, S.fb_hist, S.tile_cnt);
-    hipLaunchKernelGGL(k_topk_spill_count, dim3(kSpillBlocks, M), dim3(kBlock), 0, st, S.rows, ckey, cidx, S.cap,
-                       S.tile_cnt, S.n_tiles);
+    hipLaunchKernelGGL((k_topk_fallback<false>), dim3(kFbBlocks), dim3(kBlock), 0, st, G, E, eta, D.d, D.ld,
+                       S.n_tiles, S.n_chunks, D.M, D.k, S.rows, S.ctr, ckey, cidx, S.cap, S.fb_hist, S.tile_cnt,
+                       S.tile_off, S.chunk_off);
     const int64_t scan_per_block = (kBlock / 64) * kScanChunksPerWave;
     hipLaunchKernelGGL(k_topk_count_scan, dim3(static_cast<unsigned>((S.n_chunks + scan_per_block - 1) / scan_per_block), M),
                        dim3(kBlock), 0, st,
