@@ -1128,15 +1128,23 @@ hipError_t fused_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
     return hipGetLastError();
 }
 
-// LDS per workgroup that leaves room for 24 waves per CU with two rows per
-// wave and for 16 with four (160 KB per CU).  HBM serves the pass's mix of
-// reads and writes faster with fewer rows in flight: 16 workers x 6.3M 8-bit
-// codes, whole step 464.5 us at 32 waves, 453.0 at 24, 469.2 at 16; 32 workers
-// x 2^25, s = 15: 4662 us at 24 waves (all that its registers allow), 4609
-// at 16, 6337 at 8; 16 workers x 10^8 top-k 7210 us at 32, 7092 at 24, 7661
-// at 16.  Steps that the Infinity Cache holds are not capped.
-constexpr unsigned cap_lds(int R, int NG) {
-    return NG != 8 ? 0u : R == 2 ? 52000u : R == 4 ? 79000u : 0u;
+// Unused LDS per workgroup of `waves` waves that leaves room for about 24
+// waves per CU with two rows per wave and for about 16 with four.  HBM serves
+// the pass's mix of reads and writes faster with fewer rows in flight: 16
+// workers x 6.3M 8-bit codes, whole step 464.5 us at 32 waves, 453.0 at 24,
+// 469.2 at 16; 32 workers x 2^25, s = 15: 4662 us at 24 waves (all that its
+// registers allow), 4609 at 16, 6337 at 8; 16 workers x 10^8 top-k 7210 us at
+// 32, 7092 at 24, 7661 at 16.  The waves are those launched, which own a row:
+// counted as eight, 17 workers x 3.5M 4-bit codes (5 waves) took 317 us instead
+// of 270, 9 x 6.7M 275 instead of 251.  Steps that the Infinity Cache holds
+// are not capped.
+constexpr int kLdsPerCu = 160 * 1024;
+unsigned cap_lds(int R, int NG, int waves) {
+    const int target = NG != 8 ? 0 : R == 2 ? 24 : R == 4 ? 16 : 0;
+    if (target == 0) return 0u;
+    const int wgs = (target + waves / 2) / waves;
+    // less the kernel's own 1 KB and the allocation's rounding
+    return static_cast<unsigned>(kLdsPerCu / wgs - 1024 - 1536);
 }
 
 template <int KIND, int LB, int R, int NG, int NB = 1>
@@ -1149,7 +1157,7 @@ hipError_t split_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
     // Unused LDS that caps the workgroups per CU of a step that streams from
     // HBM (see fused_by_m).
     const double bytes = 16.0 * P.desc.M * static_cast<double>(P.desc.ld);
-    const unsigned cap = bytes > kInfinityCacheBytes ? cap_lds(R, NG) : 0u;
+    const unsigned cap = bytes > kInfinityCacheBytes ? cap_lds(R, NG, static_cast<int>(block.x / 64)) : 0u;
     // Only 8-bit planes have a second store kind (store_fields32).
     constexpr bool kTwoKinds = (KIND == kQsgd || KIND == kMbit) && LB == 8;
     if (kTwoKinds && a.stream_msg)
