@@ -28,10 +28,17 @@ namespace {
 
 enum { kSign = DQGAN_SIGN, kQsgd = DQGAN_QSGD, kTopk = DQGAN_TOPK, kIdentity = DQGAN_IDENTITY, kMbit = DQGAN_MBIT };
 
+template <int V>
+using Const = std::integral_constant<int, V>;
+
+// How the fused pass treats the caches: its matrices kept in them (see
+// data_streams), streamed past them, or streamed together with the message.
+enum { kIoCached, kIoStream, kIoStreamAll };
+
 // ---------------------------------------------------------------------------
 // Pass 1: segment statistics.
 
-template <int NORM>
+template <int NORM, bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_segment_partials(const float *__restrict__ G, const float *__restrict__ E,
                                                              float eta, int64_t ld, const Piece *__restrict__ pieces,
                                                              int32_t n_pieces, double *__restrict__ partial,
@@ -53,8 +60,8 @@ __global__ __launch_bounds__(kBlock) void k_segment_partials(const float *__rest
         for (int u = 0; u < U; ++u) {
             const int64_t q = qb + u * kBlock;
             if (q < q1) {
-                gv[u] = ld_stream(g + 4 * q);
-                ev[u] = ld_stream(e + 4 * q);
+                gv[u] = ld_io<STREAM>(g + 4 * q);
+                ev[u] = ld_io<STREAM>(e + 4 * q);
             }
         }
 #pragma unroll
@@ -387,7 +394,7 @@ struct RowArgs {
 // encoded (more loads in flight per lane).
 constexpr int kEncRows = 4;
 
-template <int KIND, int LB>
+template <int KIND, int LB, bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_encode_rows(const float *__restrict__ G, float *__restrict__ E,
                                                         uint32_t *__restrict__ sign_plane,
                                                         uint32_t *__restrict__ level_plane, float *__restrict__ val,
@@ -408,8 +415,8 @@ __global__ __launch_bounds__(kBlock) void k_encode_rows(const float *__restrict_
         const int m = m0 + u;
         if (m < a.M) {
             const int64_t rb = static_cast<int64_t>(m) * a.ld;
-            gv[u] = ld_stream(G + rb + i0);
-            ev[u] = ld_stream(E + rb + i0);
+            gv[u] = ld_io<STREAM>(G + rb + i0);
+            ev[u] = ld_io<STREAM>(E + rb + i0);
         }
     }
 #pragma unroll
@@ -425,7 +432,7 @@ __global__ __launch_bounds__(kBlock) void k_encode_rows(const float *__restrict_
             } else {
                 cq = encode_quad<KIND>(gv[u], ev[u], a.eta, i0, a.d, m, js, crow, a.s, a.k0, a.k1, a.t);
             }
-            st_stream(E + rb + i0, cq.enew);
+            st_io<STREAM>(E + rb + i0, cq.enew);
             store_message_rt<KIND, LB>(sign_plane + m * a.sign_words, level_plane + m * a.level_words, val + rb, q,
                                        cq, a.stream_msg != 0);
         }
@@ -529,7 +536,7 @@ __global__ __launch_bounds__(kBlock) void k_fused(const float *__restrict__ G, f
 // NB > 1 (more rows than the waves can keep at once): the waves take NB
 // blocks of NG R rows in turn, the chain going on from block to block; only
 // the extrapolation operands of the earlier blocks stay in registers.
-template <int KIND, int LB, int R, int NG, int NB, bool STREAM>
+template <int KIND, int LB, int R, int NG, int NB, int IO>
 __global__ __launch_bounds__(64 * NG) void k_fused_split(const float *__restrict__ G, float *__restrict__ E,
                                                          float *__restrict__ W, float *__restrict__ WX,
                                                          float *__restrict__ Qhat, uint32_t *__restrict__ sign_plane,
@@ -550,8 +557,8 @@ __global__ __launch_bounds__(64 * NG) void k_fused_split(const float *__restrict
     f32x4 g_first, e_first;
     if constexpr (R == 1) {
         const int64_t rb0 = static_cast<int64_t>(g) * a.ld;
-        g_first = ld_stream(G + rb0 + i0);
-        e_first = ld_stream(E + rb0 + i0);
+        g_first = ld_io<IO != kIoCached>(G + rb0 + i0);
+        e_first = ld_io<IO != kIoCached>(E + rb0 + i0);
     }
     // The workgroup's first segment, by scalar loads, and whether it holds
     // all of the workgroup's columns (the common case): then a row's
@@ -572,8 +579,8 @@ __global__ __launch_bounds__(64 * NG) void k_fused_split(const float *__restrict
             const int m = (nb * NG + g) * R + r;
             if (m < M) {
                 const int64_t rb = static_cast<int64_t>(m) * a.ld;
-                const f32x4 gv = R == 1 ? g_first : ld_stream(G + rb + i0);
-                const f32x4 ev = R == 1 ? e_first : ld_stream(E + rb + i0);
+                const f32x4 gv = R == 1 ? g_first : ld_io<IO != kIoCached>(G + rb + i0);
+                const f32x4 ev = R == 1 ? e_first : ld_io<IO != kIoCached>(E + rb + i0);
                 const SegConst *crow = consts + static_cast<int64_t>(m) * a.n_seg;
                 QuadCodes cq;
                 if constexpr (KIND == kTopk) {
@@ -591,7 +598,7 @@ __global__ __launch_bounds__(64 * NG) void k_fused_split(const float *__restrict
                 if constexpr (KIND == kTopk) {
                     store_topk(val + m * ta.k, ta.idx + m * ta.k, ta.k, topk_tile_base(ta, m, blockIdx.x), i0, cq);
                 } else {
-                    store_message<KIND, LB, STREAM>(sign_plane + m * a.sign_words, level_plane + m * a.level_words,
+                    store_message<KIND, LB, IO == kIoStreamAll>(sign_plane + m * a.sign_words, level_plane + m * a.level_words,
                                                     val + rb, q, cq);
                 }
                 ph[r] = cq.phat;
@@ -985,6 +992,7 @@ __global__ __launch_bounds__(kBlock) void k_mean_rows(const float *__restrict__ 
     st4(Qhat + i0, qh);
 }
 
+template <bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_omd(const float *__restrict__ Qhat, float *__restrict__ W,
                                                 const float *__restrict__ G, const float *__restrict__ E,
                                                 float *__restrict__ WX, float eta, int64_t d, int64_t ld, int32_t M) {
@@ -1005,8 +1013,8 @@ __global__ __launch_bounds__(kBlock) void k_omd(const float *__restrict__ Qhat, 
         for (int u = 0; u < kOmdRows; ++u) {
             if (m0 + u < M) {
                 const int64_t rb = static_cast<int64_t>(m0 + u) * ld;
-                gv[u] = ld_stream(G + rb + i0);
-                ev[u] = ld_stream(E + rb + i0);
+                gv[u] = ld_io<STREAM>(G + rb + i0);
+                ev[u] = ld_io<STREAM>(E + rb + i0);
             }
         }
 #pragma unroll
@@ -1068,6 +1076,7 @@ __global__ __launch_bounds__(kBlock) void k_pack(const uint16_t *__restrict__ co
 }
 
 // Top-k worker side only (dqgan_compress_ef): one wave per (tile, worker).
+template <bool STREAM>
 __global__ __launch_bounds__(64) void k_topk_encode_rows(const float *__restrict__ G, float *__restrict__ E,
                                                          float *__restrict__ val, RowArgs a, TopkArgs ta) {
     const int m = blockIdx.y;
@@ -1075,10 +1084,10 @@ __global__ __launch_bounds__(64) void k_topk_encode_rows(const float *__restrict
     const int64_t i0 = 4 * q;
     const int64_t rb = static_cast<int64_t>(m) * a.ld;
     const TopkRow *rw = ta.rows + m;
-    const f32x4 g = ld_stream(G + rb + i0);
-    const f32x4 e = ld_stream(E + rb + i0);
+    const f32x4 g = ld_io<STREAM>(G + rb + i0);
+    const f32x4 e = ld_io<STREAM>(E + rb + i0);
     const QuadCodes cq = encode_quad_topk(g, e, a.eta, i0, a.d, rw->T, rw->I);
-    st_stream(E + rb + i0, cq.enew);
+    st_io<STREAM>(E + rb + i0, cq.enew);
     store_topk(val + m * ta.k, ta.idx + m * ta.k, ta.k, topk_tile_base(ta, m, blockIdx.x), i0, cq);
 }
 
@@ -1158,14 +1167,18 @@ hipError_t split_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
     // HBM (see fused_by_m).
     const double bytes = 16.0 * P.desc.M * static_cast<double>(P.desc.ld);
     const unsigned cap = bytes > kInfinityCacheBytes ? cap_lds(R, NG, static_cast<int>(block.x / 64)) : 0u;
+    auto go = [&](auto io) {
+        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, NB, decltype(io)::value>), grid, block, cap, st, G, E, W, WX,
+                           Qhat, w.sign, w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a, inv_m(P.desc.M), ta);
+    };
     // Only 8-bit planes have a second store kind (store_fields32).
     constexpr bool kTwoKinds = (KIND == kQsgd || KIND == kMbit) && LB == 8;
-    if (kTwoKinds && a.stream_msg)
-        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, NB, kTwoKinds>), grid, block, cap, st, G, E, W, WX, Qhat, w.sign,
-                           w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a, inv_m(P.desc.M), ta);
+    if (!data_streams(P.desc))
+        go(Const<kIoCached>{});
+    else if (kTwoKinds && a.stream_msg)
+        go(Const<kTwoKinds ? kIoStreamAll : kIoStream>{});
     else
-        hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, NB, false>), grid, block, cap, st, G, E, W, WX, Qhat, w.sign,
-                           w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a, inv_m(P.desc.M), ta);
+        go(Const<kIoStream>{});
     return hipGetLastError();
 }
 
@@ -1199,15 +1212,19 @@ hipError_t launch_segment_scales(const dqgan_plan_s &P, float eta, const float *
     const dqgan_desc &D = P.desc;
     if (!scales_in) {
         const dim3 grid(static_cast<unsigned>(P.n_pieces), static_cast<unsigned>(D.M));
+        auto go = [&](auto norm) {
+            with_stream(D, [&](auto stream) {
+                hipLaunchKernelGGL((k_segment_partials<decltype(norm)::value, decltype(stream)::value>), grid,
+                                   dim3(kBlock), 0, st, G, E, eta, D.ld, P.d_pieces, P.n_pieces, P.d_partial,
+                                   P.d_pmax);
+            });
+        };
         if (D.norm == DQGAN_L1)
-            hipLaunchKernelGGL(k_segment_partials<DQGAN_L1>, grid, dim3(kBlock), 0, st, G, E, eta, D.ld, P.d_pieces,
-                               P.n_pieces, P.d_partial, P.d_pmax);
+            go(Const<DQGAN_L1>{});
         else if (D.norm == DQGAN_L2)
-            hipLaunchKernelGGL(k_segment_partials<DQGAN_L2>, grid, dim3(kBlock), 0, st, G, E, eta, D.ld, P.d_pieces,
-                               P.n_pieces, P.d_partial, P.d_pmax);
+            go(Const<DQGAN_L2>{});
         else
-            hipLaunchKernelGGL(k_segment_partials<DQGAN_LINF>, grid, dim3(kBlock), 0, st, G, E, eta, D.ld,
-                               P.d_pieces, P.n_pieces, P.d_partial, P.d_pmax);
+            go(Const<DQGAN_LINF>{});
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
@@ -1227,8 +1244,6 @@ namespace {
 
 // Calls f(kind, field bits) with both as compile-time constants, for the
 // dense compressors: (SIGN, 0), (QSGD, 8 or 4), (MBIT, 8 or 4), (IDENTITY, 0).
-template <int V>
-using Const = std::integral_constant<int, V>;
 
 template <typename F>
 hipError_t with_dense_kind(const dqgan_plan_s &P, F &&f) {
@@ -1247,8 +1262,11 @@ hipError_t launch_encode(const dqgan_plan_s &P, float eta, uint32_t t, const flo
     const RowArgs a = row_args(P, eta, t);
     const dim3 grid(static_cast<unsigned>(P.n_tiles), static_cast<unsigned>((P.desc.M + kEncRows - 1) / kEncRows));
     return with_dense_kind(P, [&](auto K, auto L) {
-        hipLaunchKernelGGL((k_encode_rows<decltype(K)::value, decltype(L)::value>), grid, dim3(kBlock), 0, st, G, E,
-                           w.sign, w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a);
+        with_stream(P.desc, [&](auto S) {
+            hipLaunchKernelGGL((k_encode_rows<decltype(K)::value, decltype(L)::value, decltype(S)::value>), grid,
+                               dim3(kBlock), 0, st, G, E, w.sign, w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg,
+                               a);
+        });
         return hipGetLastError();
     });
 }
@@ -1339,15 +1357,20 @@ hipError_t launch_topk_encode_rows(const dqgan_plan_s &P, float eta, const float
                                    hipStream_t st) {
     const RowArgs a = row_args(P, eta, 0);
     TopkArgs ta{P.topk.rows, P.topk.tile_off, P.topk.chunk_off, P.topk.n_tiles, P.topk.n_chunks, P.desc.k, w.idx};
-    hipLaunchKernelGGL(k_topk_encode_rows, dim3(static_cast<unsigned>(P.topk.n_tiles), static_cast<unsigned>(P.desc.M)),
-                       dim3(64), 0, st, G, E, w.val, a, ta);
+    with_stream(P.desc, [&](auto S) {
+        hipLaunchKernelGGL(k_topk_encode_rows<decltype(S)::value>,
+                           dim3(static_cast<unsigned>(P.topk.n_tiles), static_cast<unsigned>(P.desc.M)), dim3(64), 0,
+                           st, G, E, w.val, a, ta);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_omd(const dqgan_plan_s &P, float eta, const float *Qhat, float *W, const float *G, const float *E,
                       float *WX, hipStream_t st) {
-    hipLaunchKernelGGL(k_omd, dim3(static_cast<unsigned>(P.n_tiles)), dim3(kBlock), 0, st, Qhat, W, G, E, WX, eta,
-                       P.desc.d, P.desc.ld, P.desc.M);
+    with_stream(P.desc, [&](auto S) {
+        hipLaunchKernelGGL(k_omd<decltype(S)::value>, dim3(static_cast<unsigned>(P.n_tiles)), dim3(kBlock), 0, st, Qhat,
+                           W, G, E, WX, eta, P.desc.d, P.desc.ld, P.desc.M);
+    });
     return hipGetLastError();
 }
 

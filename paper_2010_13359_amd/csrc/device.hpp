@@ -26,6 +26,18 @@ __device__ __forceinline__ f32x4 ld_stream(const float *p) {
 __device__ __forceinline__ void st_stream(float *p, f32x4 v) {
     __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
 }
+// The kind of access by the size of what the call touches (data_streams).
+template <bool STREAM>
+__device__ __forceinline__ f32x4 ld_io(const float *p) {
+    return STREAM ? ld_stream(p) : *reinterpret_cast<const f32x4 *>(p);
+}
+template <bool STREAM>
+__device__ __forceinline__ void st_io(float *p, f32x4 v) {
+    if (STREAM)
+        st_stream(p, v);
+    else
+        *reinterpret_cast<f32x4 *>(p) = v;
+}
 __device__ __forceinline__ f32x4 ld4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
 __device__ __forceinline__ void st4(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
 

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
 #include <vector>
 
 #include "../../include/dqgan.h"
@@ -40,6 +41,25 @@ struct alignas(8) SegConst {
 // Capacity of the MI355X Infinity Cache (memory-side, in front of HBM): the
 // fused pass streams message planes larger than this past the caches.
 constexpr double kInfinityCacheBytes = 256.0 * 1024 * 1024;
+
+// Gradients and residuals that fit the Infinity Cache are read with ordinary
+// loads, so that the pass after finds them there; larger ones are streamed past
+// it (with ordinary loads 32 workers x 2^25, s = 15, take 4790 us instead of
+// 4490).  Whole steps: 16 workers x 10^6 75.6 -> 65.8 us, 35 x 881k (247 MB)
+// 148 -> 130, 8 x 10^6 signs 43.4 -> 40.2, a worker of 8M 68.8 -> 62.6; at
+// 262 MB the gain is gone (12 x 2.7M 145 -> 148).  Stores stay streaming: the
+// evaluation points in the cache push out g and e (17 x 1.4M 106 -> 113 us).
+constexpr double kCachedBytes = 240e6;
+inline bool data_streams(const dqgan_desc &D) { return 8.0 * D.M * static_cast<double>(D.ld) > kCachedBytes; }
+
+// f(STREAM) with data_streams() as a compile-time constant.
+template <typename F>
+void with_stream(const dqgan_desc &D, F &&f) {
+    if (data_streams(D))
+        f(std::true_type{});
+    else
+        f(std::false_type{});
+}
 
 // Per-worker selection state of the top-k compressor.  Keys are the binary32
 // bit patterns of |p| (monotone in |p|).  Element i is selected iff

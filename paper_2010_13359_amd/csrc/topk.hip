@@ -479,7 +479,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_topk_band(SampleArgs a, cons
 // tests, on masks taken straight from the comparisons.
 // ROUNDS: 4 where that leaves enough workgroups to fill the chip (64 tiles, one
 // chunk of the tile scan, per workgroup), else 1 (16 tiles).
-template <int ROUNDS>
+template <int ROUNDS, bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_topk_pass(const float *__restrict__ G, const float *__restrict__ E,
                                                       float eta, int64_t d, int64_t ld, int64_t n_tiles,
                                                       const TopkRow *__restrict__ rows, uint32_t *__restrict__ ctr,
@@ -514,8 +514,8 @@ __global__ __launch_bounds__(kBlock) void k_topk_pass(const float *__restrict__ 
         for (int it = 0; it < 4; ++it) {
             const int64_t tile = t0 + 4 * round + it;
             const int64_t i0 = (tile < n_tiles ? tile : n_tiles - 1) * kTopkTile + 4 * lane;
-            gvs[it] = ld_stream(g + i0);
-            evs[it] = ld_stream(e + i0);
+            gvs[it] = ld_io<STREAM>(g + i0);
+            evs[it] = ld_io<STREAM>(e + i0);
         }
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
@@ -1997,8 +1997,11 @@ hipError_t launch_topk_select(const dqgan_plan_s &P, float eta, const float *G, 
     if (S.row_search) {
         // 16 tiles per workgroup: four times the workgroups
         const unsigned nb = static_cast<unsigned>((S.n_tiles + 15) / 16);
-        hipLaunchKernelGGL((k_topk_pass<1>), dim3(nb, M), dim3(kBlock), 0, st, G, E, eta, D.d, D.ld, S.n_tiles, S.rows,
-                           S.ctr, S.tile_cnt, ckey, cidx, S.cap, static_cast<uint2 *>(nullptr), S.n_chunks);
+        with_stream(D, [&](auto C) {
+            hipLaunchKernelGGL((k_topk_pass<1, decltype(C)::value>), dim3(nb, M), dim3(kBlock), 0, st, G, E, eta, D.d,
+                               D.ld, S.n_tiles, S.rows, S.ctr, S.tile_cnt, ckey, cidx, S.cap,
+                               static_cast<uint2 *>(nullptr), S.n_chunks);
+        });
         hipLaunchKernelGGL(k_topk_select_row, dim3(M), dim3(1024), 0, st, S.rows, S.ctr, ckey, cidx, S.cap, D.k, S.play,
                            S.fb_hist, S.tile_cnt, S.tile_off, S.chunk_off, S.n_tiles, S.n_chunks);
         hipLaunchKernelGGL((k_topk_fallback<true>), dim3(kFbBlocks), dim3(kBlock), 0, st, G, E, eta, D.d, D.ld,
@@ -2006,8 +2009,11 @@ hipError_t launch_topk_select(const dqgan_plan_s &P, float eta, const float *G, 
                            S.tile_off, S.chunk_off);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((k_topk_pass<4>), dim3(static_cast<unsigned>(S.n_chunks), M), dim3(kBlock), 0, st, G, E, eta,
-                       D.d, D.ld, S.n_tiles, S.rows, S.ctr, S.tile_cnt, ckey, cidx, S.cap, S.runs, S.n_chunks);
+    with_stream(D, [&](auto C) {
+        hipLaunchKernelGGL((k_topk_pass<4, decltype(C)::value>), dim3(static_cast<unsigned>(S.n_chunks), M),
+                           dim3(kBlock), 0, st, G, E, eta, D.d, D.ld, S.n_tiles, S.rows, S.ctr, S.tile_cnt, ckey, cidx,
+                           S.cap, S.runs, S.n_chunks);
+    });
     hipLaunchKernelGGL(k_topk_sel_top, dim3(kSelBlocks, M), dim3(kBlock), 0, st, S.rows, S.ctr, ckey, S.cap, D.k,
                        S.sel_hist);
     hipLaunchKernelGGL(k_topk_sel_collect, dim3(kSelBlocks, M), dim3(kBlock), 0, st, S.rows, S.ctr, ckey, cidx,
