@@ -389,53 +389,87 @@ struct RowArgs {
     int32_t stream_msg;               // message planes larger than the Infinity Cache: streaming stores
 };
 
-// Worker side only (dqgan_compress_ef): one quad per thread for kEncRows
-// consecutive workers, whose g and e are all loaded before the first is
-// encoded (more loads in flight per lane).
-constexpr int kEncRows = 4;
+// Row kernels off the fused step (encode, unpack, pack), bound by HBM: each thread
+// takes one quad of kUnits units, all loaded before the first is worked on
+// (one quad per thread with its own segment lookup left HBM idle: pack +
+// unpack of 16 workers x 6.3M 8-bit codes 236 us, now 132).  A unit is a row
+// (COLS = false: rows 4 y .. 4 y + 3 of one 1024-column tile, whose segments
+// are looked up once) or, for fewer than kUnits rows, a tile of one row.
+constexpr int kUnits = 4;
 
-template <int KIND, int LB, bool STREAM>
+struct UnitPos {
+    int m;
+    int64_t tile;
+    bool live;
+};
+template <bool COLS>
+__device__ __forceinline__ UnitPos unit_at(int u, int M, int64_t n_tiles) {
+    UnitPos p;
+    p.m = COLS ? static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y) * kUnits + u;
+    p.tile = COLS ? static_cast<int64_t>(blockIdx.x) * kUnits + u : static_cast<int64_t>(blockIdx.x);
+    p.live = p.m < M && p.tile < n_tiles;
+    return p;
+}
+
+// Worker side only (dqgan_compress_ef).  One worker's row in tiles of four
+// (one quad per thread, its segments found by vector loads, before): compress
+// and update of 2^25 elements, s = 255, 252 -> 237 us, of 6 10^7 489 -> 463.
+template <int KIND, int LB, bool COLS, bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_encode_rows(const float *__restrict__ G, float *__restrict__ E,
                                                         uint32_t *__restrict__ sign_plane,
                                                         uint32_t *__restrict__ level_plane, float *__restrict__ val,
                                                         const SegConst *__restrict__ consts,
                                                         const int64_t *__restrict__ off,
                                                         const int32_t *__restrict__ tile_seg, RowArgs a) {
-    const int64_t q = static_cast<int64_t>(blockIdx.x) * kQuadsPerBlock + threadIdx.x;
-    const int m0 = static_cast<int>(blockIdx.y) * kEncRows;
-    const int64_t i0 = 4 * q;
-    int js[4];
-    lookup_segments(off, tile_seg, i0, a.d, js);
-    const int j_first = __builtin_amdgcn_readfirstlane(js[0]);
-    const bool one_seg = __ballot(js[0] != j_first || js[3] != j_first) == 0;
-    const int z[4] = {0, 0, 0, 0};
-    f32x4 gv[kEncRows], ev[kEncRows];
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int64_t n_tiles = a.ld >> 10;
+    f32x4 gv[kUnits], ev[kUnits];
 #pragma unroll
-    for (int u = 0; u < kEncRows; ++u) {
-        const int m = m0 + u;
-        if (m < a.M) {
-            const int64_t rb = static_cast<int64_t>(m) * a.ld;
-            gv[u] = ld_io<STREAM>(G + rb + i0);
-            ev[u] = ld_io<STREAM>(E + rb + i0);
+    for (int u = 0; u < kUnits; ++u) {
+        const UnitPos p = unit_at<COLS>(u, a.M, n_tiles);
+        if (!p.live) continue;
+        const int64_t o = p.m * a.ld + p.tile * kElemsPerBlock + 4 * threadIdx.x;
+        gv[u] = ld_io<STREAM>(G + o);
+        ev[u] = ld_io<STREAM>(E + o);
+    }
+    // the wave's 256 columns of each unit: the first one's segment, and
+    // whether it holds them all
+    int jf[kUnits] = {0, 0, 0, 0};
+    bool one[kUnits] = {true, true, true, true};
+    if (KIND != kIdentity) {
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+            const UnitPos p = unit_at<COLS>(u, a.M, n_tiles);
+            if (!COLS && u > 0) {
+                jf[u] = jf[0];
+                one[u] = one[0];
+            } else if (p.live) {
+                const int64_t w0 = p.tile * kElemsPerBlock + 256 * wave;
+                jf[u] = uniform_segment(off, tile_seg, w0, a.d);
+                one[u] = off[jf[u] + 1] >= (w0 + 256 < a.d ? w0 + 256 : a.d);
+            }
         }
     }
 #pragma unroll
-    for (int u = 0; u < kEncRows; ++u) {
-        const int m = m0 + u;
-        if (m < a.M) {
-            const int64_t rb = static_cast<int64_t>(m) * a.ld;
-            const SegConst *crow = consts + static_cast<int64_t>(m) * a.n_seg;
-            QuadCodes cq;
-            if (one_seg) {
-                const SegConst c1[1] = {crow[j_first]};
-                cq = encode_quad<KIND>(gv[u], ev[u], a.eta, i0, a.d, m, z, c1, a.s, a.k0, a.k1, a.t);
-            } else {
-                cq = encode_quad<KIND>(gv[u], ev[u], a.eta, i0, a.d, m, js, crow, a.s, a.k0, a.k1, a.t);
-            }
-            st_io<STREAM>(E + rb + i0, cq.enew);
-            store_message_rt<KIND, LB>(sign_plane + m * a.sign_words, level_plane + m * a.level_words, val + rb, q,
-                                       cq, a.stream_msg != 0);
+    for (int u = 0; u < kUnits; ++u) {
+        const UnitPos p = unit_at<COLS>(u, a.M, n_tiles);
+        if (!p.live) continue;  // whole workgroups
+        const int64_t q = p.tile * kQuadsPerBlock + threadIdx.x, i0 = 4 * q;
+        const int64_t rb = p.m * a.ld;
+        const SegConst *crow = consts + static_cast<int64_t>(p.m) * a.n_seg;
+        QuadCodes cq;
+        if (one[u]) {
+            const SegConst c1[1] = {KIND == kIdentity ? SegConst{0.0f, 0.0f} : crow[jf[u]]};
+            const int z[4] = {0, 0, 0, 0};
+            cq = encode_quad<KIND>(gv[u], ev[u], a.eta, i0, a.d, p.m, z, c1, a.s, a.k0, a.k1, a.t);
+        } else {
+            int js[4];
+            lookup_segments(off, tile_seg, i0, a.d, js);
+            cq = encode_quad<KIND>(gv[u], ev[u], a.eta, i0, a.d, p.m, js, crow, a.s, a.k0, a.k1, a.t);
         }
+        st_io<STREAM>(E + rb + i0, cq.enew);
+        store_message_rt<KIND, LB>(sign_plane + p.m * a.sign_words, level_plane + p.m * a.level_words, val + rb, q, cq,
+                                   a.stream_msg != 0);
     }
 }
 
@@ -697,28 +731,6 @@ __device__ __forceinline__ float decode_field(uint32_t nib, uint32_t raw, int c,
     const uint32_t l = KIND == kSign ? 0u : field_level<KIND, LB>(raw, c);
     const float mag = KIND == kSign ? b : RANGE ? level_magnitude(l, b) : mul_rn(static_cast<float>(l), b);
     return __uint_as_float(__float_as_uint(mag) | field_sign<KIND, LB>(nib, raw, c));
-}
-
-// Row kernels off the fused step (unpack, pack), bound by HBM: each thread
-// takes one quad of kUnits units, all loaded before the first is worked on
-// (one quad per thread with its own segment lookup left HBM idle: pack +
-// unpack of 16 workers x 6.3M 8-bit codes 236 us, now 132).  A unit is a row
-// (COLS = false: rows 4 y .. 4 y + 3 of one 1024-column tile, whose segments
-// are looked up once) or, for fewer than kUnits rows, a tile of one row.
-constexpr int kUnits = 4;
-
-struct UnitPos {
-    int m;
-    int64_t tile;
-    bool live;
-};
-template <bool COLS>
-__device__ __forceinline__ UnitPos unit_at(int u, int M, int64_t n_tiles) {
-    UnitPos p;
-    p.m = COLS ? static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y) * kUnits + u;
-    p.tile = COLS ? static_cast<int64_t>(blockIdx.x) * kUnits + u : static_cast<int64_t>(blockIdx.x);
-    p.live = p.m < M && p.tile < n_tiles;
-    return p;
 }
 
 template <int KIND, int LB, bool COLS>
@@ -1257,17 +1269,26 @@ hipError_t with_dense_kind(const dqgan_plan_s &P, F &&f) {
 
 }  // namespace
 
+// The grid of a kernel over units (unit_at): f(COLS, grid).
+template <typename F>
+static hipError_t with_units(const dqgan_plan_s &P, F &&f) {
+    const unsigned n = static_cast<unsigned>(P.n_tiles), M = static_cast<unsigned>(P.desc.M);
+    if (P.desc.M < kUnits) return f(std::true_type{}, dim3((n + kUnits - 1) / kUnits, M));
+    return f(std::false_type{}, dim3(n, (M + kUnits - 1) / kUnits));
+}
+
 hipError_t launch_encode(const dqgan_plan_s &P, float eta, uint32_t t, const float *G, float *E, const dqgan_wire &w,
                          hipStream_t st) {
     const RowArgs a = row_args(P, eta, t);
-    const dim3 grid(static_cast<unsigned>(P.n_tiles), static_cast<unsigned>((P.desc.M + kEncRows - 1) / kEncRows));
     return with_dense_kind(P, [&](auto K, auto L) {
-        with_stream(P.desc, [&](auto S) {
-            hipLaunchKernelGGL((k_encode_rows<decltype(K)::value, decltype(L)::value, decltype(S)::value>), grid,
-                               dim3(kBlock), 0, st, G, E, w.sign, w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg,
-                               a);
+        return with_units(P, [&](auto C, dim3 grid) {
+            with_stream(P.desc, [&](auto S) {
+                hipLaunchKernelGGL(
+                    (k_encode_rows<decltype(K)::value, decltype(L)::value, decltype(C)::value, decltype(S)::value>),
+                    grid, dim3(kBlock), 0, st, G, E, w.sign, w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a);
+            });
+            return hipGetLastError();
         });
-        return hipGetLastError();
     });
 }
 
@@ -1277,14 +1298,6 @@ hipError_t launch_fused_dense(const dqgan_plan_s &P, float eta, uint32_t t, cons
     return with_dense_kind(P, [&](auto K, auto L) {
         return fused_by_m<decltype(K)::value, decltype(L)::value>(P, a, G, E, W, WX, w, Qhat, st);
     });
-}
-
-// The grid of a kernel over units (unit_at): f(COLS, grid).
-template <typename F>
-static hipError_t with_units(const dqgan_plan_s &P, F &&f) {
-    const unsigned n = static_cast<unsigned>(P.n_tiles), M = static_cast<unsigned>(P.desc.M);
-    if (P.desc.M < kUnits) return f(std::true_type{}, dim3((n + kUnits - 1) / kUnits, M));
-    return f(std::false_type{}, dim3(n, (M + kUnits - 1) / kUnits));
 }
 
 hipError_t launch_pack(const dqgan_plan_s &P, const uint16_t *codes, const float *scales, const dqgan_wire &w,
