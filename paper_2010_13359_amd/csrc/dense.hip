@@ -31,8 +31,8 @@ enum { kSign = DQGAN_SIGN, kQsgd = DQGAN_QSGD, kTopk = DQGAN_TOPK, kIdentity = D
 template <int V>
 using Const = std::integral_constant<int, V>;
 
-// How the fused pass treats the caches: its matrices kept in them (see
-// data_streams), streamed past them, or streamed together with the message.
+// How the fused pass treats the caches: its matrices read through them (see
+// second_streams), streamed past them, or streamed together with the message.
 enum { kIoCached, kIoStream, kIoStreamAll };
 
 // ---------------------------------------------------------------------------
@@ -1185,7 +1185,7 @@ hipError_t split_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
     };
     // Only 8-bit planes have a second store kind (store_fields32).
     constexpr bool kTwoKinds = (KIND == kQsgd || KIND == kMbit) && LB == 8;
-    if (!data_streams(P.desc))
+    if (!second_streams(P.desc))
         go(Const<kIoCached>{});
     else if (kTwoKinds && a.stream_msg)
         go(Const<kTwoKinds ? kIoStreamAll : kIoStream>{});
@@ -1225,7 +1225,7 @@ hipError_t launch_segment_scales(const dqgan_plan_s &P, float eta, const float *
     if (!scales_in) {
         const dim3 grid(static_cast<unsigned>(P.n_pieces), static_cast<unsigned>(D.M));
         auto go = [&](auto norm) {
-            with_stream(D, [&](auto stream) {
+            with_stream(first_streams(D), [&](auto stream) {
                 hipLaunchKernelGGL((k_segment_partials<decltype(norm)::value, decltype(stream)::value>), grid,
                                    dim3(kBlock), 0, st, G, E, eta, D.ld, P.d_pieces, P.n_pieces, P.d_partial,
                                    P.d_pmax);
@@ -1282,7 +1282,7 @@ hipError_t launch_encode(const dqgan_plan_s &P, float eta, uint32_t t, const flo
     const RowArgs a = row_args(P, eta, t);
     return with_dense_kind(P, [&](auto K, auto L) {
         return with_units(P, [&](auto C, dim3 grid) {
-            with_stream(P.desc, [&](auto S) {
+            with_stream(worker_streams(P.desc), [&](auto S) {
                 hipLaunchKernelGGL(
                     (k_encode_rows<decltype(K)::value, decltype(L)::value, decltype(C)::value, decltype(S)::value>),
                     grid, dim3(kBlock), 0, st, G, E, w.sign, w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a);
@@ -1370,7 +1370,7 @@ hipError_t launch_topk_encode_rows(const dqgan_plan_s &P, float eta, const float
                                    hipStream_t st) {
     const RowArgs a = row_args(P, eta, 0);
     TopkArgs ta{P.topk.rows, P.topk.tile_off, P.topk.chunk_off, P.topk.n_tiles, P.topk.n_chunks, P.desc.k, w.idx};
-    with_stream(P.desc, [&](auto S) {
+    with_stream(worker_streams(P.desc), [&](auto S) {
         hipLaunchKernelGGL(k_topk_encode_rows<decltype(S)::value>,
                            dim3(static_cast<unsigned>(P.topk.n_tiles), static_cast<unsigned>(P.desc.M)), dim3(64), 0,
                            st, G, E, w.val, a, ta);
@@ -1380,7 +1380,7 @@ hipError_t launch_topk_encode_rows(const dqgan_plan_s &P, float eta, const float
 
 hipError_t launch_omd(const dqgan_plan_s &P, float eta, const float *Qhat, float *W, const float *G, const float *E,
                       float *WX, hipStream_t st) {
-    with_stream(P.desc, [&](auto S) {
+    with_stream(worker_streams(P.desc), [&](auto S) {
         hipLaunchKernelGGL(k_omd<decltype(S)::value>, dim3(static_cast<unsigned>(P.n_tiles)), dim3(kBlock), 0, st, Qhat,
                            W, G, E, WX, eta, P.desc.d, P.desc.ld, P.desc.M);
     });

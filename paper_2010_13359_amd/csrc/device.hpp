@@ -26,7 +26,7 @@ __device__ __forceinline__ f32x4 ld_stream(const float *p) {
 __device__ __forceinline__ void st_stream(float *p, f32x4 v) {
     __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
 }
-// The kind of access by the size of what the call touches (data_streams).
+// The kind of access by the size of what the call touches (first_streams, second_streams).
 template <bool STREAM>
 __device__ __forceinline__ f32x4 ld_io(const float *p) {
     return STREAM ? ld_stream(p) : *reinterpret_cast<const f32x4 *>(p);

@@ -42,20 +42,31 @@ struct alignas(8) SegConst {
 // fused pass streams message planes larger than this past the caches.
 constexpr double kInfinityCacheBytes = 256.0 * 1024 * 1024;
 
-// Gradients and residuals that fit the Infinity Cache are read with ordinary
-// loads, so that the pass after finds them there; larger ones are streamed past
-// it (with ordinary loads 32 workers x 2^25, s = 15, take 4790 us instead of
-// 4490).  Whole steps: 16 workers x 10^6 75.6 -> 65.8 us, 35 x 881k (247 MB)
-// 148 -> 130, 8 x 10^6 signs 43.4 -> 40.2, a worker of 8M 68.8 -> 62.6; at
-// 262 MB the gain is gone (12 x 2.7M 145 -> 148).  Stores stay streaming: the
-// evaluation points in the cache push out g and e (17 x 1.4M 106 -> 113 us).
-constexpr double kCachedBytes = 240e6;
-inline bool data_streams(const dqgan_desc &D) { return 8.0 * D.M * static_cast<double>(D.ld) > kCachedBytes; }
+// The first pass of a step (statistics, top-k counts) reads g and e with
+// ordinary loads where the Infinity Cache holds them, so that the second pass
+// finds them there; the second does so too where the cache also holds what it
+// writes, and the next steps' data.  Otherwise loads stream past the caches
+// (with ordinary loads 32 workers x 2^25, s = 15, take 4790 us instead of
+// 4490).  Whole steps over three states in turn, both passes streaming / the
+// first ordinary / both ordinary, by the size of g and e: 40 MB 33.6 / 33.2 /
+// 28.5 us, 70 MB 48.5 / 47.2 / 44.0, 100 MB 67.1 / 63.5 / 67.4, 140 MB 81.6 /
+// 76.7 / 96.4, 187 MB 112.6 / 103.6 / 132.5, 230 MB 142.4 / 131.3 / 160.0 (4-bit
+// codes; top-k alike); at 262 MB the first line's gain is gone.
+constexpr double kFirstPassCached = 240e6, kBothPassesCached = 85e6;
+inline double data_bytes(const dqgan_desc &D) { return 8.0 * D.M * static_cast<double>(D.ld); }
+inline bool first_streams(const dqgan_desc &D) { return data_bytes(D) > kFirstPassCached; }
+inline bool second_streams(const dqgan_desc &D) { return data_bytes(D) > kBothPassesCached; }
 
-// f(STREAM) with data_streams() as a compile-time constant.
+// The worker's own calls (encode, update) touch the rows once more each: 20 MB
+// ordinary / streaming 32.5 / 34.0 us for a worker's iteration, 60 MB 67.0 / 65.5,
+// 64 MB 71.9 / 69.3 (s = 255).
+constexpr double kWorkerCached = 40e6;
+inline bool worker_streams(const dqgan_desc &D) { return data_bytes(D) > kWorkerCached; }
+
+// f(STREAM) with `streams` as a compile-time constant.
 template <typename F>
-void with_stream(const dqgan_desc &D, F &&f) {
-    if (data_streams(D))
+void with_stream(bool streams, F &&f) {
+    if (streams)
         f(std::true_type{});
     else
         f(std::false_type{});

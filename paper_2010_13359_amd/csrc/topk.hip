@@ -1997,7 +1997,7 @@ hipError_t launch_topk_select(const dqgan_plan_s &P, float eta, const float *G, 
     if (S.row_search) {
         // 16 tiles per workgroup: four times the workgroups
         const unsigned nb = static_cast<unsigned>((S.n_tiles + 15) / 16);
-        with_stream(D, [&](auto C) {
+        with_stream(first_streams(D), [&](auto C) {
             hipLaunchKernelGGL((k_topk_pass<1, decltype(C)::value>), dim3(nb, M), dim3(kBlock), 0, st, G, E, eta, D.d,
                                D.ld, S.n_tiles, S.rows, S.ctr, S.tile_cnt, ckey, cidx, S.cap,
                                static_cast<uint2 *>(nullptr), S.n_chunks);
@@ -2009,7 +2009,7 @@ hipError_t launch_topk_select(const dqgan_plan_s &P, float eta, const float *G, 
                            S.tile_off, S.chunk_off);
         return hipGetLastError();
     }
-    with_stream(D, [&](auto C) {
+    with_stream(first_streams(D), [&](auto C) {
         hipLaunchKernelGGL((k_topk_pass<4, decltype(C)::value>), dim3(static_cast<unsigned>(S.n_chunks), M),
                            dim3(kBlock), 0, st, G, E, eta, D.d, D.ld, S.n_tiles, S.rows, S.ctr, S.tile_cnt, ckey, cidx,
                            S.cap, S.runs, S.n_chunks);
