@@ -813,10 +813,12 @@ __global__ __launch_bounds__(kBlock) void k_unpack(const uint32_t *__restrict__ 
 // term).  Elements at or beyond d are summed with the rest and dropped at the
 // end.
 //
-// Bound by the vector ALU: 6 operations per decoded element (field, its
-// conversion, the product, the sign's shift and OR, the sum) take 166 us of
-// the 199 us at 32 workers x 2^25, s = 15 (262 us before: 8.8 operations, a
-// bound test per row, and constants from a launch of their own).
+// Bound by the vector ALU: about 5 operations per decoded element (a byte's
+// conversion, the product, the sign's shift and OR, the sum; 4-bit fields are
+// made bytes eight at a time: with each extracted by itself 185 us instead of
+// 179 at 32 workers x 2^25, s = 15, 57 instead of 52 at 16 x 20M 4-bit codes).
+// 262 us with 8.8 operations, a bound test per row, and constants from a launch
+// of their own.
 // 16 workers x 6.3M 8-bit codes 46 -> 30 us, 8 x 10^6 15.3 -> 11.5.
 // Held to 80 registers for six waves per SIMD the kernel spills: 274 us.
 constexpr int kAggQuads = 4;
@@ -844,9 +846,29 @@ struct AggFields {
             }
         }
     }
-    // element c of quad k
+    // 4-bit fields as bytes, the even ones of a word and the odd ones: a byte's
+    // conversion is one operation with its extraction.  (The empty asm keeps
+    // the compiler from extracting each field from the word again.)
+    uint32_t even[kWords], odd[kWords];
+    __device__ __forceinline__ void split() {
+        if (LB != 4) return;
+        constexpr uint32_t mask = KIND == kMbit ? 0x07070707u : 0x0F0F0F0Fu;
+#pragma unroll
+        for (int c = 0; c < kWords; ++c) {
+            even[c] = fw[c] & mask;
+            odd[c] = (fw[c] >> 4) & mask;
+            asm("" : "+v"(even[c]), "+v"(odd[c]));
+        }
+    }
+    // element c of quad k (after split())
     template <bool RANGE>
     __device__ __forceinline__ float value(int k, int c, float b) const {
+        if constexpr (LB == 4) {
+            const int w = (k >> 1) % kWords, f = 4 * (k & 1) + c;  // field f of word w
+            const uint32_t l = ((f & 1 ? odd[w] : even[w]) >> (8 * (f >> 1))) & 0xFFu;
+            const float mag = RANGE ? level_magnitude(l, b) : mul_rn(static_cast<float>(l), b);
+            return __uint_as_float(__float_as_uint(mag) | field_sign<KIND, LB>(sg >> (8 * (k >> 1)), fw[w], f));
+        }
         const uint32_t raw = KIND == kSign ? 0u : kWords == 4 ? fw[k % kWords] : fw[(k >> 1) % kWords] >> (16 * (k & 1));
         return decode_field<KIND, LB, RANGE>(sg >> (4 * k), raw, c, b);
     }
@@ -860,9 +882,10 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint32_t *__restrict
                                                       const int64_t *__restrict__ off,
                                                       const int32_t *__restrict__ tile_seg, RowArgs a, float invM) {
     typedef AggFields<KIND, LB> Fields;
-    // 2 bytes a row and thread: more rows in flight (32 workers x 2^25 signs:
-    // 108 us with eight, 116 with four)
-    constexpr int kAggRows = KIND == kSign ? 8 : 4;
+    // One plane a row: more rows in flight (32 workers x 2^25 signs 108 us with
+    // eight, 116 with four; 16 x 20M 8-bit codes 79, 81; 4-bit codes 51.5, 53.8;
+    // two planes, s = 255: 88.5, 87)
+    constexpr int kAggRows = KIND == kQsgd ? 4 : 8;
     const int lane = threadIdx.x & 63;
     const int64_t tile = static_cast<int64_t>(blockIdx.x) * (kBlock / 64) +
                          __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -904,7 +927,8 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint32_t *__restrict
             if (lane < n)
                 bl = decode_const<KIND>(scale[static_cast<int64_t>(mb + lane) * a.n_seg + j], a.s);
             auto rows = [&](auto range) {
-                auto add_row = [&](const Fields &f, int r) {
+                auto add_row = [&](Fields &f, int r) {
+                    f.split();
                     const float b = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(bl), r));
 #pragma unroll
                     for (int k = 0; k < kAggQuads; ++k) {
@@ -952,6 +976,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint32_t *__restrict
         for (int m = 0; m < a.M; ++m) {
             Fields f;
             f.load(sign_plane, level_plane, a, m, g16);
+            f.split();
             int jc = j0;
 #pragma unroll
             for (int k = 0; k < kAggQuads; ++k) {
