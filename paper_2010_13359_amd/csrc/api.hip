@@ -173,9 +173,7 @@ dqgan_status dqgan_plan_create(const dqgan_desc *desc, dqgan_plan *out) {
             if (n > P->max_tile_segs) P->max_tile_segs = n;
         }
     }
-    const int64_t piece = static_cast<int64_t>(desc->M) * (d / dq::kPieceElems) >= dq::kPieceBlocksForLong
-                              ? dq::kPieceElems
-                              : dq::kPieceElems / 2;
+    const int64_t piece = dq::piece_elems(desc->M, d);
     std::vector<Piece> pieces;
     std::vector<int32_t> seg_piece(static_cast<size_t>(S) + 1);
     for (int32_t j = 0; j < S; ++j) {
@@ -191,6 +189,10 @@ dqgan_status dqgan_plan_create(const dqgan_desc *desc, dqgan_plan *out) {
         return DQGAN_EINVAL;
     }
     P->n_pieces = static_cast<int32_t>(pieces.size());
+    for (int32_t j = 0; j < S; ++j) {
+        const int32_t n = seg_piece[static_cast<size_t>(j) + 1] - seg_piece[static_cast<size_t>(j)];
+        if (n > P->max_seg_pieces) P->max_seg_pieces = n;
+    }
 
     hipError_t e = hipSuccess;
     if (e == hipSuccess) e = upload(&P->d_off, P->offsets);
@@ -203,6 +205,8 @@ dqgan_status dqgan_plan_create(const dqgan_desc *desc, dqgan_plan *out) {
         if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&P->d_pmax), npart * sizeof(float));
         if (e == hipSuccess)
             e = hipMalloc(reinterpret_cast<void **>(&P->d_consts), static_cast<size_t>(desc->M) * S * sizeof(dq::SegConst));
+        if (e == hipSuccess) e = hipMemset(dq::arrivals(*P), 0, static_cast<size_t>(desc->M) * S * sizeof(uint32_t));
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     }
     if (e == hipSuccess && desc->kind == DQGAN_TOPK) e = dq::topk_alloc(*P);
     if (e != hipSuccess) {

@@ -6,8 +6,9 @@
 // Passes over HBM per iteration:
 //   1. segment statistics: per (worker, segment) sum |p|, sum p^2 or max |p|
 //      of p = fl(fl(eta g) + e), one workgroup per piece, binary64 partials;
-//      a tiny kernel then combines the partials of each segment in piece
-//      order (deterministic) into the scale and the quantizer constants.
+//      a tiny kernel, or the last workgroup of a segment with few pieces,
+//      combines the partials of each segment in piece order (deterministic)
+//      into the scale and the quantizer constants.
 //   2. the fused apply pass (k_fused_split): a workgroup covers 256 elements
 //      of all M workers, its waves splitting the workers; each lane encodes
 //      one quad of 4 elements per worker row, writes e_t and the message,
@@ -38,11 +39,79 @@ enum { kIoCached, kIoStream, kIoStreamAll };
 // ---------------------------------------------------------------------------
 // Pass 1: segment statistics.
 
+// The per-segment constants (SegConst) of a scale: SIGN the scale; QSGD, MBIT
+// fl(s/(u sigma)) and fl(u sigma/s), negated when u = 2^64 (sigma < 2^-64),
+// zeros for sigma = 0 or not finite.  Quotients of two binary32 values
+// computed in binary64 and rounded to binary32 equal the correctly rounded
+// binary32 quotient (53 >= 2*24 + 2).
+__device__ __forceinline__ SegConst seg_const(int kind, int levels, float sc) {
+    SegConst c{sc, 0.0f};
+    if (kind == kQsgd || kind == kMbit) {
+        c.a = 0.0f;
+        if (sc > 0.0f && sc <= 3.402823466e38f) {
+            const bool tiny = sc < 0x1.0p-64f;
+            // u * sigma is exact: a power of two times a binary32 value
+            const double sd = static_cast<double>(sc) * (tiny ? 0x1.0p64 : 1.0), lv = static_cast<double>(levels);
+            c.a = static_cast<float>(lv / sd);
+            c.b = static_cast<float>(sd / lv);
+            if (tiny) {
+                c.a = -c.a;
+                c.b = -c.b;
+            }
+        }
+    }
+    return c;
+}
+
+// The scale from the whole segment's sum or maximum; n = its elements.
+__device__ __forceinline__ float scale_of(int norm, double s, float mx, int64_t n) {
+    return norm == DQGAN_LINF ? mx
+           : norm == DQGAN_L1 ? static_cast<float>(s / static_cast<double>(n))
+                              : static_cast<float>(sqrt(s));
+}
+
+// The scale of one (worker, segment) from its pieces' partials, by a whole
+// wave: lane l adds the segment's pieces p0 + l, p0 + l + 64, ... in order,
+// then a fixed butterfly combines the lanes (every lane gets the result).
+// `partial` and `pmax` point at the worker's row and are read at device scope
+// (the statistics pass may have written them in the same launch).
+__device__ __forceinline__ float segment_scale(int norm, const double *partial, const float *pmax, int p0, int p1,
+                                               int64_t n) {
+    const int lane = threadIdx.x & 63;
+    double s = 0.0;
+    float mx = 0.0f;
+    if (norm == DQGAN_LINF) {
+        for (int p = p0 + lane; p < p1; p += 64)
+            mx = fmaxf(mx, __hip_atomic_load(pmax + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    } else {
+        for (int p = p0 + lane; p < p1; p += 64)
+            s += __hip_atomic_load(partial + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    }
+    return scale_of(norm, s, mx, n);
+}
+
+// What the statistics pass writes.
+struct StatsOut {
+    double *partial;  // [M][n_pieces] per piece
+    float *pmax;
+    // [M][n_seg] workgroups of the segment that have arrived (zero between
+    // launches); NULL: k_finalize derives the scales
+    uint32_t *arrived;
+    const int32_t *seg_piece;
+    const int64_t *off;
+    float *scale;
+    SegConst *consts;
+    int32_t n_seg, kind, norm, levels;
+};
+
 template <int NORM, bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_segment_partials(const float *__restrict__ G, const float *__restrict__ E,
                                                              float eta, int64_t ld, const Piece *__restrict__ pieces,
-                                                             int32_t n_pieces, double *__restrict__ partial,
-                                                             float *__restrict__ pmax) {
+                                                             int32_t n_pieces, StatsOut out) {
     const int pc = blockIdx.x;
     const int m = blockIdx.y;
     const Piece P = pieces[pc];
@@ -98,56 +167,46 @@ __global__ __launch_bounds__(kBlock) void k_segment_partials(const float *__rest
         shm[wave] = mx;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int64_t o = static_cast<int64_t>(m) * n_pieces + pc;
-        partial[o] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-        pmax[o] = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
-    }
-}
-
-// The per-segment constants (SegConst) of a scale: SIGN the scale; QSGD, MBIT
-// fl(s/(u sigma)) and fl(u sigma/s), negated when u = 2^64 (sigma < 2^-64),
-// zeros for sigma = 0 or not finite.  Quotients of two binary32 values
-// computed in binary64 and rounded to binary32 equal the correctly rounded
-// binary32 quotient (53 >= 2*24 + 2).
-__device__ __forceinline__ SegConst seg_const(int kind, int levels, float sc) {
-    SegConst c{sc, 0.0f};
-    if (kind == kQsgd || kind == kMbit) {
-        c.a = 0.0f;
-        if (sc > 0.0f && sc <= 3.402823466e38f) {
-            const bool tiny = sc < 0x1.0p-64f;
-            // u * sigma is exact: a power of two times a binary32 value
-            const double sd = static_cast<double>(sc) * (tiny ? 0x1.0p64 : 1.0), lv = static_cast<double>(levels);
-            c.a = static_cast<float>(lv / sd);
-            c.b = static_cast<float>(sd / lv);
-            if (tiny) {
-                c.a = -c.a;
-                c.b = -c.b;
-            }
+    if (wave != 0) return;
+    s = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    mx = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
+    const int64_t row = static_cast<int64_t>(m) * n_pieces;
+    if (!out.arrived) {
+        if (threadIdx.x == 0) {
+            out.partial[row + pc] = s;
+            out.pmax[row + pc] = mx;
         }
+        return;
     }
-    return c;
-}
-
-// The scale of one (worker, segment) from its pieces' partials, by a whole
-// wave: lane l adds the segment's pieces p0 + l, p0 + l + 64, ... in order,
-// then a fixed butterfly combines the lanes (every lane gets the result).
-// `partial` and `pmax` point at the worker's row; n = the segment's elements.
-__device__ __forceinline__ float segment_scale(int norm, const double *__restrict__ partial,
-                                               const float *__restrict__ pmax, int p0, int p1, int64_t n) {
-    const int lane = threadIdx.x & 63;
-    if (norm == DQGAN_LINF) {
-        float mx = 0.0f;
-        for (int p = p0 + lane; p < p1; p += 64) mx = fmaxf(mx, pmax[p]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-        return mx;
+    // Few pieces: the last workgroup of the segment to arrive derives its
+    // scale, in place of a launch of its own.
+    const int64_t ms = static_cast<int64_t>(m) * out.n_seg + P.seg;
+    const int p0 = out.seg_piece[P.seg], p1 = out.seg_piece[P.seg + 1];
+    const int64_t n = out.off[P.seg + 1] - out.off[P.seg];
+    if (p1 - p0 > 1) {
+        // The partial goes out at device scope, the wait holds the arrival
+        // back until it is there, and the last to arrive reads all of them at
+        // device scope: no cache is written back or dropped, which an
+        // agent-scope fence does over the XCD's whole L2.
+        uint32_t before = 0;
+        if (threadIdx.x == 0) {
+            if (NORM == DQGAN_LINF)
+                __hip_atomic_store(out.pmax + row + pc, mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+                __hip_atomic_store(out.partial + row + pc, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            before = __hip_atomic_fetch_add(out.arrived + ms, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (__builtin_amdgcn_readfirstlane(static_cast<int>(before)) != p1 - p0 - 1) return;
+        asm volatile("" ::: "memory");
+        if (threadIdx.x == 0)  // zero again for the next launch
+            __hip_atomic_store(out.arrived + ms, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    double s = 0.0;
-    for (int p = p0 + lane; p < p1; p += 64) s += partial[p];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    return norm == DQGAN_L1 ? static_cast<float>(s / static_cast<double>(n)) : static_cast<float>(sqrt(s));
+    const float sc = p1 - p0 > 1 ? segment_scale(out.norm, out.partial + row, out.pmax + row, p0, p1, n)
+                                 : scale_of(out.norm, s, mx, n);
+    if (threadIdx.x != 0) return;
+    out.scale[ms] = sc;
+    out.consts[ms] = seg_const(out.kind, out.levels, sc);
 }
 
 // The scale and constants of every (worker, segment), one wave each, from
@@ -1244,16 +1303,29 @@ hipError_t fused_by_m(const dqgan_plan_s &P, const RowArgs &a, const float *G, f
 
 }  // namespace
 
+// Whether the statistics pass derives the scales itself.  Small workloads gain
+// a launch (4 workers x 65536 signs 18.5 -> 15.5 us, 16 x 500k 37.1 -> 35.6, a
+// worker of 200k 28.5 -> 24).  The arrivals of a segment are atomics on one
+// address, one after the other, and each holds its workgroup's place on the CU:
+// with more of them the launch is cheaper (8 x 10^6, 33 pieces a segment, 39.6
+// -> 41.3 us; 129 pieces 56; 16 x 6.3M 431 -> 451).
+static bool stats_few(const dqgan_plan_s &P) {
+    constexpr int kFewPieces = 16, kFewBlocks = 1024;
+    return P.max_seg_pieces <= kFewPieces && static_cast<int64_t>(P.desc.M) * P.n_pieces <= kFewBlocks;
+}
+
 hipError_t launch_segment_scales(const dqgan_plan_s &P, float eta, const float *G, const float *E,
                                  const float *scales_in, float *scale_out, hipStream_t st) {
     const dqgan_desc &D = P.desc;
     if (!scales_in) {
         const dim3 grid(static_cast<unsigned>(P.n_pieces), static_cast<unsigned>(D.M));
+        const bool few = stats_few(P);
+        const StatsOut out{P.d_partial, P.d_pmax, few ? arrivals(P) : nullptr, P.d_seg_piece, P.d_off,
+                           scale_out, P.d_consts, D.n_seg, D.kind, D.norm, P.level_count};
         auto go = [&](auto norm) {
             with_stream(first_streams(D), [&](auto stream) {
                 hipLaunchKernelGGL((k_segment_partials<decltype(norm)::value, decltype(stream)::value>), grid,
-                                   dim3(kBlock), 0, st, G, E, eta, D.ld, P.d_pieces, P.n_pieces, P.d_partial,
-                                   P.d_pmax);
+                                   dim3(kBlock), 0, st, G, E, eta, D.ld, P.d_pieces, P.n_pieces, out);
             });
         };
         if (D.norm == DQGAN_L1)
@@ -1263,7 +1335,7 @@ hipError_t launch_segment_scales(const dqgan_plan_s &P, float eta, const float *
         else
             go(Const<DQGAN_LINF>{});
         hipError_t err = hipGetLastError();
-        if (err != hipSuccess) return err;
+        if (err != hipSuccess || few) return err;
     }
     const int64_t n = static_cast<int64_t>(D.M) * D.n_seg;
     // one wave per (worker, segment)

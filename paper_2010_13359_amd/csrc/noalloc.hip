@@ -89,7 +89,8 @@ struct SegTable {
 __global__ __launch_bounds__(dq::kBlock) void k_noalloc_tables(SegTable T, int64_t *__restrict__ off,
                                                                int32_t *__restrict__ seg_piece,
                                                                int32_t *__restrict__ tile_seg,
-                                                               dq::Piece *__restrict__ pieces) {
+                                                               dq::Piece *__restrict__ pieces,
+                                                               uint32_t *__restrict__ arrivals, int64_t n_arrivals) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * dq::kBlock + threadIdx.x;
     if (i <= T.n_seg) {
         off[i] = T.off[i];
@@ -104,6 +105,7 @@ __global__ __launch_bounds__(dq::kBlock) void k_noalloc_tables(SegTable T, int64
         }
         tile_seg[i] = lo;
     }
+    if (i < n_arrivals) arrivals[i] = 0u;
     if (i < T.n_pieces) {
         int lo = 0, hi = T.n_seg - 1;  // the segment j with first_piece[j] <= i < first_piece[j + 1]
         while (lo < hi) {
@@ -181,8 +183,7 @@ extern "C" dqgan_status dqgan_step_fused_noalloc(const dqgan_desc *desc, float e
 
     // Pieces as dqgan_plan_create cuts them (the scales then equal the
     // plan's bit for bit).
-    T.piece = static_cast<int64_t>(D.M) * (D.d / dq::kPieceElems) >= dq::kPieceBlocksForLong ? dq::kPieceElems
-                                                                                          : dq::kPieceElems / 2;
+    T.piece = dq::piece_elems(D.M, D.d);
     int64_t n_pieces = 0;
     for (int32_t j = 0; j < D.n_seg; ++j) {
         T.first_piece[j] = static_cast<int32_t>(n_pieces);
@@ -214,6 +215,9 @@ extern "C" dqgan_status dqgan_step_fused_noalloc(const dqgan_desc *desc, float e
     P.d_tile_seg = reinterpret_cast<int32_t *>(base + L.tile_seg);
     P.d_pieces = reinterpret_cast<dq::Piece *>(base + L.pieces);
     P.n_pieces = T.n_pieces;
+    for (int32_t j = 0; j < D.n_seg; ++j)
+        if (T.first_piece[j + 1] - T.first_piece[j] > P.max_seg_pieces)
+            P.max_seg_pieces = T.first_piece[j + 1] - T.first_piece[j];
     P.d_partial = reinterpret_cast<double *>(base + L.partial);
     P.d_pmax = reinterpret_cast<float *>(base + L.pmax);
     P.d_consts = reinterpret_cast<dq::SegConst *>(base + L.consts);
@@ -221,8 +225,11 @@ extern "C" dqgan_status dqgan_step_fused_noalloc(const dqgan_desc *desc, float e
     int64_t n_threads = T.n_tiles;
     if (T.n_pieces > n_threads) n_threads = T.n_pieces;
     if (T.n_seg + 1 > n_threads) n_threads = T.n_seg + 1;
+    const int64_t n_arrivals = static_cast<int64_t>(D.M) * D.n_seg;
+    if (n_arrivals > n_threads) n_threads = n_arrivals;
     hipLaunchKernelGGL(k_noalloc_tables, dim3(static_cast<unsigned>((n_threads + dq::kBlock - 1) / dq::kBlock)),
-                       dim3(dq::kBlock), 0, st, T, P.d_off, P.d_seg_piece, P.d_tile_seg, P.d_pieces);
+                       dim3(dq::kBlock), 0, st, T, P.d_off, P.d_seg_piece, P.d_tile_seg, P.d_pieces,
+                       dq::arrivals(P), n_arrivals);
     if (hipGetLastError() != hipSuccess) return DQGAN_EHIP;
     if (D.kind != DQGAN_IDENTITY && dq::launch_segment_scales(P, eta, G, E, nullptr, out->scale, st) != hipSuccess)
         return DQGAN_EHIP;

@@ -11,20 +11,24 @@
 
 namespace dq {
 
-// A contiguous run of one segment of a row, at most kPieceElems long (half
-// that for workloads with few pieces); the norm pass reduces one piece per
-// workgroup.  Pieces never cross segments.
+// A contiguous run of one segment of a row, at most piece_elems() long; the
+// statistics pass reduces one piece per workgroup.  Pieces never cross
+// segments.
 struct Piece {
     int64_t start;
     int32_t len;
     int32_t seg;
 };
-constexpr int64_t kPieceElems = 32768;
-// Below this many (worker, piece) workgroups the pieces are halved: the
-// statistics pass over 32 workers x 2^25 elements ran 1.5 % faster with
-// 32768-element pieces than with 16384, over 16 workers x 6.3M elements 2 %
-// slower.
-constexpr int64_t kPieceBlocksForLong = 16384;
+// 32768 elements from 16384 workgroups up: the statistics pass over 32 workers
+// x 2^25 elements ran 1.5 % faster with them than with 16384, over 16 workers
+// x 6.3M elements 2 % slower.  Below kPieceBlocksSmall, four elements less than
+// 16384, so that a piece that does not start at a quad takes no trip of its
+// own for one quad (8 x 10^6 signs 40.3 -> 39.8 us).
+constexpr int64_t kPieceBlocksForLong = 16384, kPieceBlocksSmall = 2048;
+inline int64_t piece_elems(int64_t M, int64_t d) {
+    if (M * (d / 32768) >= kPieceBlocksForLong) return 32768;
+    return M * (d / 16384) >= kPieceBlocksSmall ? 16384 : 16380;
+}
 
 // Per (worker, segment) constants of the segment-scaled compressors.
 // SIGN: a = the scale.  QSGD, MBIT (equation qsgd): a = fl(s / (u sigma))
@@ -169,12 +173,23 @@ struct dqgan_plan_s {
     int32_t max_tile_segs = 1;      // most segments that meet one tile (1024 elements)
     dq::Piece *d_pieces = nullptr;  // [n_pieces]
     int32_t n_pieces = 0;
+    int32_t max_seg_pieces = 0;     // most pieces of one segment
     int32_t *d_seg_piece = nullptr;  // [n_seg + 1] first piece of each segment
     double *d_partial = nullptr;     // [M][n_pieces] partial sums (L1, L2^2)
     float *d_pmax = nullptr;         // [M][n_pieces] partial maxima (Linf)
     dq::SegConst *d_consts = nullptr;  // [M][n_seg] per-segment constants
     dq::TopkScratch topk;
 };
+
+namespace dq {
+
+// Arrivals of the statistics pass per (worker, segment): in the partials' array
+// that the plan's norm leaves unused (each segment has at least one piece).
+inline uint32_t *arrivals(const dqgan_plan_s &P) {
+    return P.desc.norm == DQGAN_LINF ? reinterpret_cast<uint32_t *>(P.d_partial) : reinterpret_cast<uint32_t *>(P.d_pmax);
+}
+
+}  // namespace dq
 
 namespace dq {
 
