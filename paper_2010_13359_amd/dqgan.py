@@ -101,6 +101,10 @@ def _ptr(t, name="tensor", nbytes=0, dtypes=None, device=None):
     holding at least `nbytes` bytes.  None passes as NULL."""
     if t is None:
         return None
+    # the usual case by the fewest attribute reads; what fails here is named below
+    if (isinstance(t, torch.Tensor) and t.is_cuda and (dtypes is None or t.dtype in dtypes)
+            and (device is None or t.get_device() == device) and t.is_contiguous() and t.nbytes >= nbytes):
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s: expected a torch.Tensor" % name)
     if not t.is_cuda:
@@ -111,15 +115,13 @@ def _ptr(t, name="tensor", nbytes=0, dtypes=None, device=None):
         raise TypeError("%s: dtype %s, expected %s" % (name, t.dtype, " or ".join(str(d) for d in dtypes)))
     if device is not None and t.device.index != device:
         raise ValueError("%s: on cuda:%s, the plan is on cuda:%d" % (name, t.device.index, device))
-    if t.numel() * t.element_size() < nbytes:
-        raise ValueError("%s: %d bytes, the plan needs %d" % (name, t.numel() * t.element_size(), nbytes))
-    return ctypes.c_void_p(t.data_ptr())
+    raise ValueError("%s: %d bytes, the plan needs %d" % (name, t.nbytes, nbytes))
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is None:  # the current device's current stream, without a Stream object
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 class Plan:
@@ -192,14 +194,13 @@ class Wire:
     def struct(self, plan):
         """The dqgan_wire of these planes; each plane the plan's compressor
         uses must be present and large enough."""
-        planes = (("sign", self.sign, U32), ("level", self.level, U32), ("scale", self.scale, F32),
-                  ("val", self.val, F32), ("idx", self.idx, U32))
+        planes = (("wire.sign", self.sign, U32), ("wire.level", self.level, U32), ("wire.scale", self.scale, F32),
+                  ("wire.val", self.val, F32), ("wire.idx", self.idx, U32))
         ptrs = []
         for (name, t, dt), need in zip(planes, plan._wire_bytes):
             if need and t is None:
-                raise ValueError("wire.%s: the plan's compressor needs this plane (%d bytes)" % (name, need))
-            p = _ptr(t, "wire." + name, need, dt, plan.device)
-            ptrs.append(None if p is None else p.value)
+                raise ValueError("%s: the plan's compressor needs this plane (%d bytes)" % (name, need))
+            ptrs.append(_ptr(t, name, need, dt, plan.device))
         return WireStruct(*ptrs)
 
 
