@@ -16,7 +16,7 @@
 //      is chained through LDS; the last wave of the chain applies
 //      w_t = w_{t-1} - q-hat; every wave then writes its rows' evaluation
 //      points w_t - (fl(eta g) + e_t).  k_fused (one lane walks all M rows)
-//      serves M > 128.
+//      serves M > 256.
 #include <algorithm>
 #include <type_traits>
 
@@ -1284,9 +1284,10 @@ hipError_t split_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
 // 17 <= M <= 32, 8 waves x 4 rows beats 16 x 2 by 2-3 % although it runs 6
 // rather than 8 waves per SIMD; M <= 8 (cache-resident sizes) keeps one row
 // per wave; for 65 <= M <= 128, 16 waves x 8 rows (4 waves per SIMD) is a
-// third faster than the one-lane kernel.  Beyond 128 rows no register-resident
-// split fits (16 rows per lane need more than the 128 VGPRs a 16-wave
-// workgroup allows), and the one-lane-per-quad kernel serves.
+// third faster than the one-lane kernel; for 129 <= M <= 256 four blocks of
+// 16 waves x 4 rows in turn take 1376 us where the one-lane kernel takes 1759
+// (256 x 10^6, s = 255).  Beyond 256 rows the operands do not fit the 128
+// registers of a 16-wave workgroup, and the one-lane-per-quad kernel serves.
 template <int KIND, int LB>
 hipError_t fused_by_m(const dqgan_plan_s &P, const RowArgs &a, const float *G, float *E, float *W, float *WX,
                       const dqgan_wire &w, float *Qhat, hipStream_t st) {

@@ -63,9 +63,12 @@ inline bool second_streams(const dqgan_desc &D) { return data_bytes(D) > kBothPa
 
 // The worker's own calls (encode, update) touch the rows once more each: 20 MB
 // ordinary / streaming 32.5 / 34.0 us for a worker's iteration, 60 MB 67.0 / 65.5,
-// 64 MB 71.9 / 69.3 (s = 255).
+// 64 MB 71.9 / 69.3 (s = 255).  The identity has no statistics: its encode is the
+// first pass (120 MB 97.0 / 104.4, 160 MB 133.9 / 138.9).
 constexpr double kWorkerCached = 40e6;
-inline bool worker_streams(const dqgan_desc &D) { return data_bytes(D) > kWorkerCached; }
+inline bool worker_streams(const dqgan_desc &D) {
+    return D.kind == DQGAN_IDENTITY ? first_streams(D) : data_bytes(D) > kWorkerCached;
+}
 
 // f(STREAM) with `streams` as a compile-time constant.
 template <typename F>
