@@ -255,13 +255,19 @@ __device__ __forceinline__ void write_band(const uint32_t *sub, const uint32_t *
     }
 }
 
+// Waits for the wave's own global stores and atomics.  Called by every wave
+// ahead of the barrier behind which one thread's release fence publishes the
+// workgroup's results: the compiler puts no such wait before a barrier, and the
+// wait inside the fence covers the operations of that thread's wave alone.
+__device__ __forceinline__ void drain_writes() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Whether this workgroup is the last of n to arrive at *done; everything the
 // others wrote before arriving is then visible to it.  Called by every thread.
-// One thread's fences stand for the workgroup (the barriers order the other
-// threads' accesses before and after them): an agent-scope release writes the
-// whole L2 back, and one per wave made the sample 125 and the band 82 us over
-// 16 rows of 10^8.
+// Every wave drains its writes; after the barrier one thread's fences stand for
+// the workgroup: an agent-scope release writes the whole L2 back, and one per
+// wave made the sample 125 and the band 82 us over 16 rows of 10^8.
 __device__ __forceinline__ bool last_to_arrive(uint32_t *done, uint32_t n, uint32_t *flag) {
+    drain_writes();
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();
@@ -1079,6 +1085,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_fallback(const float *__restric
             }
             // this workgroup's chunks are finished: its results first, then
             // the count (one thread's fences, as in last_to_arrive)
+            drain_writes();
             __syncthreads();
             if (threadIdx.x == 0) {
                 __threadfence();
