@@ -98,8 +98,8 @@ __device__ __forceinline__ float segment_scale(int norm, const double *partial, 
 struct StatsOut {
     double *partial;  // [M][n_pieces] per piece
     float *pmax;
-    // [M][n_seg] workgroups of the segment that have arrived (zero between
-    // launches); NULL: k_finalize derives the scales
+    // FEW: [M][n_seg] workgroups of the segment that have arrived (zero between
+    // launches)
     uint32_t *arrived;
     const int32_t *seg_piece;
     const int64_t *off;
@@ -108,7 +108,11 @@ struct StatsOut {
     int32_t n_seg, kind, norm, levels;
 };
 
-template <int NORM, bool STREAM>
+// FEW: the last workgroup of a segment derives its scale (stats_few); else
+// k_finalize does.  A variant of its own: pieces of 100 elements are all head
+// and tail, and with the choice made at run time 16 workers x 4M elements in
+// such segments took 574 us instead of 506.
+template <int NORM, bool STREAM, bool FEW>
 __global__ __launch_bounds__(kBlock) void k_segment_partials(const float *__restrict__ G, const float *__restrict__ E,
                                                              float eta, int64_t ld, const Piece *__restrict__ pieces,
                                                              int32_t n_pieces, StatsOut out) {
@@ -167,17 +171,17 @@ __global__ __launch_bounds__(kBlock) void k_segment_partials(const float *__rest
         shm[wave] = mx;
     }
     __syncthreads();
-    if (wave != 0) return;
-    s = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-    mx = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
     const int64_t row = static_cast<int64_t>(m) * n_pieces;
-    if (!out.arrived) {
+    if constexpr (!FEW) {
         if (threadIdx.x == 0) {
-            out.partial[row + pc] = s;
-            out.pmax[row + pc] = mx;
+            out.partial[row + pc] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+            out.pmax[row + pc] = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
         }
         return;
     }
+    if (wave != 0) return;
+    s = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    mx = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
     // Few pieces: the last workgroup of the segment to arrive derives its
     // scale, in place of a launch of its own.
     const int64_t ms = static_cast<int64_t>(m) * out.n_seg + P.seg;
@@ -1321,12 +1325,18 @@ hipError_t launch_segment_scales(const dqgan_plan_s &P, float eta, const float *
     if (!scales_in) {
         const dim3 grid(static_cast<unsigned>(P.n_pieces), static_cast<unsigned>(D.M));
         const bool few = stats_few(P);
-        const StatsOut out{P.d_partial, P.d_pmax, few ? arrivals(P) : nullptr, P.d_seg_piece, P.d_off,
+        const StatsOut out{P.d_partial, P.d_pmax, arrivals(P), P.d_seg_piece, P.d_off,
                            scale_out, P.d_consts, D.n_seg, D.kind, D.norm, P.level_count};
+        auto launch = [&](auto norm, auto stream, auto few_c) {
+            hipLaunchKernelGGL((k_segment_partials<decltype(norm)::value, decltype(stream)::value, decltype(few_c)::value>),
+                               grid, dim3(kBlock), 0, st, G, E, eta, D.ld, P.d_pieces, P.n_pieces, out);
+        };
         auto go = [&](auto norm) {
             with_stream(first_streams(D), [&](auto stream) {
-                hipLaunchKernelGGL((k_segment_partials<decltype(norm)::value, decltype(stream)::value>), grid,
-                                   dim3(kBlock), 0, st, G, E, eta, D.ld, P.d_pieces, P.n_pieces, out);
+                if (few)
+                    launch(norm, stream, std::true_type{});
+                else
+                    launch(norm, stream, std::false_type{});
             });
         };
         if (D.norm == DQGAN_L1)
