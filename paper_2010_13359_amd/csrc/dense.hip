@@ -368,18 +368,21 @@ __device__ __forceinline__ void store_topk(float *__restrict__ val_row, uint32_t
     }
 }
 
-__device__ __forceinline__ void lookup_segments(const int64_t *__restrict__ off, const int32_t *__restrict__ tile_seg,
-                                                int64_t i0, int64_t d, int js[4]) {
+// The segments of the quad at i0 (elements at or beyond d: the last one's), from
+// a segment j that does not lie behind them.
+__device__ __forceinline__ void walk_segments(const int64_t *__restrict__ off, int j, int64_t i0, int64_t d,
+                                              int js[4]) {
     const int64_t last = d - 1;
-    int j = tile_seg[i0 >> 10];
-    j = seg_from(off, j, i0 < last ? i0 : last);
-    js[0] = j;
 #pragma unroll
-    for (int c = 1; c < 4; ++c) {
+    for (int c = 0; c < 4; ++c) {
         const int64_t i = i0 + c;
         j = seg_from(off, j, i < last ? i : last);
         js[c] = j;
     }
+}
+__device__ __forceinline__ void lookup_segments(const int64_t *__restrict__ off, const int32_t *__restrict__ tile_seg,
+                                                int64_t i0, int64_t d, int js[4]) {
+    walk_segments(off, tile_seg[i0 >> 10], i0, d, js);
 }
 
 // The segment of element min(i, d - 1), for an i that is the same for the
@@ -660,13 +663,14 @@ __global__ __launch_bounds__(64 * NG) void k_fused_split(const float *__restrict
     // The workgroup's first segment, by scalar loads, and whether it holds
     // all of the workgroup's columns (the common case): then a row's
     // constants are one scalar load, and no lane looks up its elements'
-    // segments (a chain of dependent vector loads before the first row).
+    // segments (a chain of dependent vector loads before the first row); else
+    // the lanes walk on from the workgroup's first segment, not from the tile's.
     const int64_t c0 = static_cast<int64_t>(blockIdx.x) * 256;
     const int64_t c1 = c0 + 256 < a.d ? c0 + 256 : a.d;
     const int j_first = KIND == kTopk || KIND == kIdentity ? 0 : uniform_segment(off, tile_seg, c0, a.d);
     const bool one_seg = KIND == kTopk || KIND == kIdentity || off[j_first + 1] >= c1;
     int js[4] = {j_first, j_first, j_first, j_first};
-    if (!one_seg) lookup_segments(off, tile_seg, i0, a.d, js);
+    if (!one_seg) walk_segments(off, j_first, i0, a.d, js);
     f32x4 ph[R], xs[NB * R];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
@@ -1245,9 +1249,13 @@ hipError_t fused_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
 // registers allow), 4609 at 16, 6337 at 8; 16 workers x 10^8 top-k 7210 us at
 // 32, 7092 at 24, 7661 at 16.  The waves are those launched, which own a row:
 // counted as eight, 17 workers x 3.5M 4-bit codes (5 waves) took 317 us instead
-// of 270, 9 x 6.7M 275 instead of 251.  Steps that the Infinity Cache holds
-// are not capped.
+// of 270, 9 x 6.7M 275 instead of 251.  Not capped: steps that the Infinity
+// Cache holds, and plans of short segments, whose waves wait for look-ups and
+// constants rather than for HBM (apply pass with the cap / without: 32 workers
+// x 4M, s = 15, segments of 150 550 / 487 us, 601 502 / 452, 2401 470 / 434,
+// 5001 and more within 1 %; 16 workers, signs, 150 229 / 209, 601 205 / 209).
 constexpr int kLdsPerCu = 160 * 1024;
+constexpr int64_t kShortSegment = 4096;  // mean elements below which a plan's segments are short
 unsigned cap_lds(int R, int NG, int waves) {
     const int target = NG != 8 ? 0 : R == 2 ? 24 : R == 4 ? 16 : 0;
     if (target == 0) return 0u;
@@ -1264,9 +1272,10 @@ hipError_t split_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
     // only the waves that own a row
     const dim3 grid(static_cast<unsigned>(P.n_tiles * 4)), block(64 * static_cast<unsigned>(std::min((P.desc.M + R - 1) / R, NG)));
     // Unused LDS that caps the workgroups per CU of a step that streams from
-    // HBM (see fused_by_m).
+    // HBM (see cap_lds).
     const double bytes = 16.0 * P.desc.M * static_cast<double>(P.desc.ld);
-    const unsigned cap = bytes > kInfinityCacheBytes ? cap_lds(R, NG, static_cast<int>(block.x / 64)) : 0u;
+    const bool short_segs = KIND != kTopk && KIND != kIdentity && P.desc.d < kShortSegment * P.desc.n_seg;
+    const unsigned cap = bytes > kInfinityCacheBytes && !short_segs ? cap_lds(R, NG, static_cast<int>(block.x / 64)) : 0u;
     auto go = [&](auto io) {
         hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, NB, decltype(io)::value>), grid, block, cap, st, G, E, W, WX,
                            Qhat, w.sign, w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a, inv_m(P.desc.M), ta);
