@@ -516,6 +516,7 @@ __global__ __launch_bounds__(kBlock) void k_encode_rows(const float *__restrict_
             }
         }
     }
+    int js[4];  // the quad's segments where the wave's columns hold several; rows of one tile look them up once
 #pragma unroll
     for (int u = 0; u < kUnits; ++u) {
         const UnitPos p = unit_at<COLS>(u, a.M, n_tiles);
@@ -529,8 +530,7 @@ __global__ __launch_bounds__(kBlock) void k_encode_rows(const float *__restrict_
             const int z[4] = {0, 0, 0, 0};
             cq = encode_quad<KIND>(gv[u], ev[u], a.eta, i0, a.d, p.m, z, c1, a.s, a.k0, a.k1, a.t);
         } else {
-            int js[4];
-            lookup_segments(off, tile_seg, i0, a.d, js);
+            if (COLS || u == 0) walk_segments(off, jf[u], i0, a.d, js);
             cq = encode_quad<KIND>(gv[u], ev[u], a.eta, i0, a.d, p.m, js, crow, a.s, a.k0, a.k1, a.t);
         }
         st_io<STREAM>(E + rb + i0, cq.enew);
