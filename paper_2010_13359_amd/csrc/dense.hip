@@ -889,7 +889,25 @@ __global__ __launch_bounds__(kBlock) void k_unpack(const uint32_t *__restrict__ 
 // 16 workers x 6.3M 8-bit codes 46 -> 30 us, 8 x 10^6 15.3 -> 11.5.
 // Held to 80 registers for six waves per SIMD the kernel spills: 274 us.
 constexpr int kAggQuads = 4;
-constexpr int kAggSegs = 8;  // segments of a wave up to which each takes a pass of its own
+// Rows loaded before the first is decoded.  One plane a row: more rows in flight (32
+// workers x 2^25 signs 108 us with eight, 116 with four; 16 x 20M 8-bit codes 79,
+// 81; 4-bit codes 51.5, 53.8; two planes, s = 255: 88.5, 87).
+constexpr int agg_rows(int kind) { return kind == kQsgd ? 4 : 8; }
+// Segments of a wave up to which each takes a pass of its own over the wave's
+// messages; with more every element looks its constant up, in one pass that
+// costs about 12 of the others (s levels 16, 8-bit codes 8).  A row outside a full
+// batch costs 2 to 4 in one; the batches of four have a row's worth of overhead
+// or two.  4M elements, a pass per segment / look-ups: 32 workers, signs, 8
+// segments a tile 94 / 174 us, 12 133 / 197; s = 255, 8 182 / 277, 13 294 / 342;
+// 8-bit codes, 8 173 / 189, 12 256 / 224; 6 workers, signs, 8 47 / 41, s = 255,
+// 8 56 / 48; 4 workers, 8-bit codes, 8 43 / 33, 4 26 / 26.
+int agg_segs(int kind, int level_bits, int M) {
+    const int left = M % agg_rows(kind), full = M - left;
+    const int n = kind == kQsgd                      ? 16 * M / (full + 4 * left + 2)
+                  : kind == kMbit && level_bits == 8 ? 8 * M / (full + 3 * left)
+                                                     : 12 * M / (full + 2 * left);
+    return std::max(n, 5);  // 1 worker, s = 255, 3 segments 12.4 / 15.4 us
+}
 
 template <int KIND, int LB>
 struct AggFields {
@@ -947,12 +965,10 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint32_t *__restrict
                                                       const float *__restrict__ scale, float *__restrict__ Qhat,
                                                       const SegConst *__restrict__ consts,
                                                       const int64_t *__restrict__ off,
-                                                      const int32_t *__restrict__ tile_seg, RowArgs a, float invM) {
+                                                      const int32_t *__restrict__ tile_seg, RowArgs a, float invM,
+                                                      int few_segs) {
     typedef AggFields<KIND, LB> Fields;
-    // One plane a row: more rows in flight (32 workers x 2^25 signs 108 us with
-    // eight, 116 with four; 16 x 20M 8-bit codes 79, 81; 4-bit codes 51.5, 53.8;
-    // two planes, s = 255: 88.5, 87)
-    constexpr int kAggRows = KIND == kQsgd ? 4 : 8;
+    constexpr int kAggRows = agg_rows(KIND);
     const int lane = threadIdx.x & 63;
     const int64_t tile = static_cast<int64_t>(blockIdx.x) * (kBlock / 64) +
                          __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -1029,7 +1045,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint32_t *__restrict
                 rows(std::true_type{});
         }
     };
-    if (!MANY || j1 - j0 < kAggSegs) {
+    if (!MANY || j1 - j0 < few_segs) {
         // one segment (the common case) or a few: each decodes the wave's
         // messages once and keeps its own elements
         for (int j = j0; j <= j1; ++j) {
@@ -1038,21 +1054,24 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint32_t *__restrict
             keep(off[j], off[j + 1]);
         }
     } else if constexpr (MANY) {
-        // many short segments: every element its own constant
+        // many short segments: every element its own constant, its segment
+        // looked up once for all rows (walked again for every row, 32 workers x
+        // 4M 8-bit codes in segments of 100 took 327 us instead of 85)
+        int js[kAggQuads][4];
+#pragma unroll
+        for (int k = 0; k < kAggQuads; ++k)
+            walk_segments(off, k == 0 ? j0 : js[k > 0 ? k - 1 : 0][3], 16 * g16 + 4 * k, a.d, js[k]);
         restart();
         for (int m = 0; m < a.M; ++m) {
             Fields f;
             f.load(sign_plane, level_plane, a, m, g16);
             f.split();
-            int jc = j0;
+            const SegConst *crow = consts + static_cast<int64_t>(m) * a.n_seg;
 #pragma unroll
             for (int k = 0; k < kAggQuads; ++k) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const int64_t i = 16 * g16 + 4 * k + c;
-                    jc = seg_from(off, jc, i < a.d ? i : a.d - 1);
-                    const int64_t o = static_cast<int64_t>(m) * a.n_seg + jc;
-                    const float b = KIND == kSign ? consts[o].a : consts[o].b;
+                    const float b = KIND == kSign ? crow[js[k][c]].a : crow[js[k][c]].b;
                     set_elem(acc[k], c, add_rn(elem(acc[k], c), f.template value<true>(k, c, b)));
                 }
             }
@@ -1457,7 +1476,8 @@ hipError_t launch_aggregate_dense(const dqgan_plan_s &P, const dqgan_wire &w, fl
     // Tiles of more segments than a wave takes one by one: the variant that
     // looks up every element's constant, derived once per (worker, segment)
     // by a launch of its own (16 quotients per thread and row otherwise).
-    const bool many = P.max_tile_segs > kAggSegs;
+    const int few_segs = agg_segs(P.desc.kind, P.level_bits, P.desc.M);
+    const bool many = P.max_tile_segs > few_segs;
     if (many) {
         hipError_t err = launch_consts_from_scales(P, w.scale, st);
         if (err != hipSuccess) return err;
@@ -1469,7 +1489,7 @@ hipError_t launch_aggregate_dense(const dqgan_plan_s &P, const dqgan_wire &w, fl
             auto go = [&](auto many_c) {
                 hipLaunchKernelGGL((k_aggregate<decltype(K)::value, decltype(L)::value, decltype(many_c)::value>), grid,
                                    dim3(kBlock), 0, st, w.sign, w.level, w.scale, Qhat, P.d_consts, P.d_off,
-                                   P.d_tile_seg, a, im);
+                                   P.d_tile_seg, a, im, few_segs);
                 return hipGetLastError();
             };
             return many ? go(std::true_type{}) : go(std::false_type{});

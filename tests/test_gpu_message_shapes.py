@@ -65,3 +65,37 @@ def test_messages(kind, norm, levels, layout, M):
     got = Q.cpu().numpy()
     assert np.array_equal(got[:d].view(np.uint32), mean.view(np.uint32)) and np.all(got[d:] == 0)
     plan.close()
+
+
+@pytest.mark.parametrize("kind,norm,levels", KINDS)
+@pytest.mark.parametrize("M", [4, 6, 16])
+def test_average_by_segments_per_tile(kind, norm, levels, M):
+    """The server average on both sides of the segments per tile up to which
+    each segment is summed in a pass of its own (4 to 12, by messages and
+    workers), next to a tile of one segment."""
+    import torch
+    from paper_2010_13359_amd import dqgan
+    rng = np.random.default_rng(M)
+    top = (1 << (levels - 1)) - 1 if kind == "mbit" else levels
+    d, ld = 2047, 2048
+    for n in range(3, 15):
+        print("case", kind, levels, "M", M, "segments", n, flush=True)
+        offs = [1024 * j // n for j in range(n)] + [1024, d]
+        codes = (rng.integers(0, top + 1, (M, ld)) | (rng.integers(0, 2, (M, ld)) << 15)).astype(np.uint16)
+        scales = rng.lognormal(-5.0, 1.0, (M, len(offs) - 1)).astype(np.float32)
+        scales[0, 1] = 0.0
+        scales[-1, 2] = 1e-25       # below 2^-64: the scaled constants
+        plan = dqgan.Plan(d, M, kind, seg_offsets=offs, norm=norm, levels=levels, seed=1)
+        wire = plan.new_wire("cuda")
+        Q = torch.full((ld,), float("nan"), device="cuda")
+        dqgan.pack(plan, to_dev(codes.view(np.int16)), to_dev(scales), wire)
+        dqgan.aggregate(plan, wire, Q)
+        torch.cuda.synchronize()
+        exp = _expect(kind, levels, codes[:, :d], scales, offs)
+        total = exp[0].copy()
+        for m in range(1, M):
+            total = total + exp[m]
+        mean = (total.astype(np.float64) / M).astype(np.float32)
+        got = Q.cpu().numpy()
+        assert np.array_equal(got[:d].view(np.uint32), mean.view(np.uint32)) and np.all(got[d:] == 0)
+        plan.close()
