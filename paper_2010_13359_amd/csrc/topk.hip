@@ -909,11 +909,16 @@ __global__ __launch_bounds__(1024) void k_topk_sel_finish(TopkRow *__restrict__ 
 // over the whole row, one histogram slot per digit, then the row's tile
 // counts, in one launch that is a short read of the row flags when no row
 // fell back -- the usual case (seven launches before: 2.2 to 5 us each).
-// The workgroups claim a phase's chunks (64 tiles) from a counter and go on to
-// the next phase when the number of finished chunks is complete.  A workgroup
-// thus waits only for chunks that running workgroups have claimed, never for
+// The workgroups take the digits one after the other over all fallen-back rows
+// and claim a row's units (a few tiles) from a counter; a workgroup goes on to
+// the row's next digit when the number of finished units is complete.  It thus
+// waits only for units that running workgroups have claimed, never for
 // a workgroup that has not started (one that starts late finds nothing left
 // to claim): the waits end whatever part of the grid the device runs at once.
+// Digit by digit over all rows, and units small enough for every workgroup:
+// row by row in units of 64 tiles, a step with 16 zero rows of 200k took 3570 us
+// (with seven launches 1510, now 750), with 64 of 10^6 16200 (9600, 5600), with
+// one of 10^6 403 (234, 212).
 constexpr int kMaxRows = 1024;  // the library's largest worker count
 
 struct FbState {
@@ -921,13 +926,14 @@ struct FbState {
     int next;  // the digit whose histogram comes next, or kSelectPasses when decided
 };
 
-__device__ FbState fb_replay(int64_t k, const uint32_t *__restrict__ f6, int upto) {
-    FbState s{static_cast<uint32_t>(k), 0u, 0u, 0u, 0xFFFFFFFFu, 0};
-    for (int pass = 0; pass < kSelectPasses; ++pass) {
-        if (pass >= upto) {
-            s.next = pass;
-            return s;
-        }
+// The state (at first fb_start) brought up to the digits below `upto`, whose
+// histograms are complete, by one wave.
+__device__ __forceinline__ FbState fb_start(int64_t k) {
+    return FbState{static_cast<uint32_t>(k), 0u, 0u, 0u, 0xFFFFFFFFu, 0};
+}
+__device__ FbState fb_advance(FbState s, const uint32_t *__restrict__ f6, int upto) {
+    while (s.next < upto) {
+        const int pass = s.next++;
         uint32_t bin = 0, above = 0;
         wave_find_desc(f6 + pass * kDigitBins, bins_of(pass), s.rank, bin, above);
         const uint32_t n_bin = f6[pass * kDigitBins + bin];
@@ -935,14 +941,10 @@ __device__ FbState fb_replay(int64_t k, const uint32_t *__restrict__ f6, int upt
         add_prefix(pass, bin, s.kprefix, s.iprefix);
         if (pass == 2) {
             s.T = s.kprefix;
-            if (s.rank == n_bin) {  // every element with key T is taken
-                s.next = kSelectPasses;
-                return s;
-            }
+            if (s.rank == n_bin) s.next = kSelectPasses;  // every element with key T is taken
         }
         if (pass == 5) s.I = ~s.iprefix;
     }
-    s.next = kSelectPasses;
     return s;
 }
 
@@ -979,6 +981,57 @@ __device__ void scan_tiles(const uint16_t *__restrict__ cnt, uint16_t *__restric
     if (threadIdx.x == 0) *total = carry;
 }
 
+// One unit (the tiles t0 .. t0 + unit - 1 below n_tiles, the waves side by side)
+// of the full-row search: the digit PASS of the elements still in play added to
+// the LDS histogram h, or (PASS == kSelectPasses) the tiles' counts.  PASS is a
+// compile-time value: with the digit's choice made per element at run time the
+// loop was bound by branches (30M elements 465 us per digit).
+template <int PASS>
+__device__ __forceinline__ void fb_unit(const float *__restrict__ g, const float *__restrict__ e, float eta, int64_t d,
+                                        int64_t n_tiles, int64_t t0, int unit, const FbState &s, uint32_t *h,
+                                        uint16_t *__restrict__ cnt_row) {
+    // tiles per wave and round, loaded before the first is examined
+    constexpr int kWaves = kBlock / 64, kU = 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    for (int w0 = wave; w0 < unit; w0 += kU * kWaves) {
+        f32x4 gv[kU], ev[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (w0 + u * kWaves >= unit) break;  // whole waves
+            const int64_t tile = t0 + w0 + u * kWaves;
+            const int64_t i0 = (tile < n_tiles ? tile : n_tiles - 1) * kTopkTile + 4 * lane;
+            gv[u] = ld4(g + i0);
+            ev[u] = ld4(e + i0);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int64_t tile = t0 + w0 + u * kWaves;
+            if (w0 + u * kWaves >= unit || tile >= n_tiles) break;  // whole waves
+            uint32_t n = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t i = tile * kTopkTile + 4 * lane + q;
+                const uint32_t key = key_of(elem(gv[u], q), elem(ev[u], q), eta);
+                const uint32_t ni = ~static_cast<uint32_t>(i);
+                if constexpr (PASS == kSelectPasses)
+                    n += __popcll(__ballot(i < d && (key > s.T || (key == s.T && static_cast<uint32_t>(i) <= s.I))));
+                else
+                    if (i < d && in_play(PASS, key, ni, s.kprefix, s.iprefix)) atomicAdd(&h[digit_of(PASS, key, ni)], 1u);
+            }
+            if (PASS == kSelectPasses && lane == 0) cnt_row[tile] = static_cast<uint16_t>(n);
+        }
+    }
+}
+template <int PASS>
+__device__ __forceinline__ void fb_unit_of_pass(int pass, const float *__restrict__ g, const float *__restrict__ e,
+                                                float eta, int64_t d, int64_t n_tiles, int64_t t0, int unit,
+                                                const FbState &s, uint32_t *h, uint16_t *__restrict__ cnt_row) {
+    if (pass == PASS)
+        fb_unit<PASS>(g, e, eta, d, n_tiles, t0, unit, s, h, cnt_row);
+    else if constexpr (PASS < kSelectPasses)
+        fb_unit_of_pass<PASS + 1>(pass, g, e, eta, d, n_tiles, t0, unit, s, h, cnt_row);
+}
+
 // SCAN: the tile scan of a fallen-back row too (short rows, whose other tile
 // scans the search kernel does); otherwise the spilled candidates (stored from
 // the top of the list) of the rows whose search decided are added to their
@@ -995,11 +1048,15 @@ __global__ __launch_bounds__(kBlock) void k_topk_fallback(const float *__restric
                                                           uint16_t *__restrict__ tile_off,
                                                           uint32_t *__restrict__ chunk_off) {
     __shared__ uint32_t h[kDigitBins];
-    __shared__ FbState st;
+    // the states of the first rows that fell back, from digit to digit (others
+    // go through all digits before each time)
+    constexpr int kKept = 64;
+    __shared__ FbState st, kept[kKept];
+    // 1: the row fell back; 2: and its key and index are decided by the first
+    // three digits
     __shared__ int fb_rows[kMaxRows], sp_rows[kMaxRows];
     __shared__ int n_fb, n_sp;
     __shared__ uint32_t claimed, is_last;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (threadIdx.x == 0) n_fb = n_sp = 0;
     __syncthreads();
     // the rows are looked at in parallel; those that fell back are then taken
@@ -1031,75 +1088,79 @@ __global__ __launch_bounds__(kBlock) void k_topk_fallback(const float *__restric
         }
     }
     if (n_fb == 0) return;
-    for (int m = 0; m < M; ++m) {
-        if (!fb_rows[m]) continue;
-        uint32_t *f6 = fb_hist + static_cast<int64_t>(m) * kSelectPasses * kDigitBins;
-        uint32_t *c = ctr + static_cast<int64_t>(m) * kRowCtrWords;
-        const float *g = G + static_cast<int64_t>(m) * ld;
-        const float *e = E + static_cast<int64_t>(m) * ld;
-        // phases 0 .. 5: the digits; 6: the tile counts
-        for (int pass = 0; pass <= kSelectPasses; ++pass) {
+    // tiles per unit: a tile per wave at least, a chunk of kTopkChunkTiles at
+    // most, about two units per workgroup over all rows in between
+    const int64_t share = n_fb * n_tiles / (2 * static_cast<int64_t>(gridDim.x));
+    int unit = kBlock / 64;
+    while (unit < kTopkChunkTiles && 2 * unit <= share) unit *= 2;
+    const int64_t n_units = (n_tiles + unit - 1) / unit;
+    // phases 0 .. 5: the digits; 6: the tile counts
+    for (int pass = 0; pass <= kSelectPasses; ++pass) {
+        const bool recount = pass == kSelectPasses;
+        int nth = -1;  // of the fallen-back rows
+        for (int m = 0; m < M; ++m) {
+            if (fb_rows[m] == 0) continue;
+            ++nth;
+            if (fb_rows[m] == 2 && !recount) continue;
+            uint32_t *f6 = fb_hist + static_cast<int64_t>(m) * kSelectPasses * kDigitBins;
+            uint32_t *c = ctr + static_cast<int64_t>(m) * kRowCtrWords;
+            if (pass > 0) {
+                // the row's digit before this one is complete (two more passes
+                // of a row that was decided by its third: nothing to wait for)
+                if (threadIdx.x == 0) {
+                    const int before = fb_rows[m] == 2 ? 2 : pass - 1;
+                    while (__hip_atomic_load(c + kCtrFinished + before, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                           n_units)
+                        __builtin_amdgcn_s_sleep(8);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                }
+                __syncthreads();
+            }
             if (threadIdx.x < 64) {
-                const FbState s = fb_replay(k, f6, pass);
-                if (threadIdx.x == 0) st = s;
+                const FbState s = fb_advance(pass > 0 && nth < kKept ? kept[nth] : fb_start(k), f6, pass);
+                if (threadIdx.x == 0) {
+                    st = s;
+                    if (nth < kKept) kept[nth] = s;
+                }
             }
             __syncthreads();
             const FbState s = st;
-            const bool recount = pass == kSelectPasses;
             if (!recount && s.next != pass) {  // decided without this digit, for every workgroup alike
-                __syncthreads();               // st is rewritten
+                if (threadIdx.x == 0) fb_rows[m] = 2;
+                __syncthreads();  // st is rewritten, fb_rows[m] read again
                 continue;
             }
             const int nb = recount ? 0 : bins_of(pass);
-            for (int b = threadIdx.x; b < nb; b += kBlock) h[b] = 0u;
-            uint32_t mine = 0;  // chunks this workgroup took
+            const float *g = G + static_cast<int64_t>(m) * ld;
+            const float *e = E + static_cast<int64_t>(m) * ld;
+            uint32_t mine = 0;  // units this workgroup took
             for (;;) {
                 __syncthreads();
                 if (threadIdx.x == 0) claimed = atomicAdd(c + kCtrClaim + pass, 1u);
                 __syncthreads();
-                if (claimed >= n_chunks) break;
-                ++mine;
-                for (int w = wave; w < kTopkChunkTiles; w += kBlock / 64) {
-                    const int64_t tile = static_cast<int64_t>(claimed) * kTopkChunkTiles + w;
-                    if (tile >= n_tiles) break;  // whole waves
-                    const int64_t i0 = tile * kTopkTile + 4 * lane;
-                    const f32x4 gv = ld4(g + i0), ev = ld4(e + i0);
-                    uint32_t n = 0;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int64_t i = i0 + q;
-                        const uint32_t key = key_of(elem(gv, q), elem(ev, q), eta);
-                        const uint32_t ni = ~static_cast<uint32_t>(i);
-                        if (recount)
-                            n += __popcll(__ballot(i < d && (key > s.T || (key == s.T && static_cast<uint32_t>(i) <= s.I))));
-                        else if (i < d && in_play(pass, key, ni, s.kprefix, s.iprefix))
-                            atomicAdd(&h[digit_of(pass, key, ni)], 1u);
-                    }
-                    if (recount && lane == 0)
-                        tile_cnt[static_cast<int64_t>(m) * n_tiles + tile] = static_cast<uint16_t>(n);
+                if (claimed >= n_units) break;
+                if (mine++ == 0) {
+                    for (int b = threadIdx.x; b < nb; b += kBlock) h[b] = 0u;
+                    __syncthreads();
                 }
+                fb_unit_of_pass<0>(pass, g, e, eta, d, n_tiles, static_cast<int64_t>(claimed) * unit, unit, s, h,
+                                   tile_cnt + static_cast<int64_t>(m) * n_tiles);
             }
-            if (mine) {
-                for (int b = threadIdx.x; b < nb; b += kBlock)
-                    if (h[b]) atomicAdd(&f6[pass * kDigitBins + b], h[b]);
-            }
-            // this workgroup's chunks are finished: its results first, then
+            if (mine == 0) continue;
+            for (int b = threadIdx.x; b < nb; b += kBlock)
+                if (h[b]) atomicAdd(&f6[pass * kDigitBins + b], h[b]);
+            // this workgroup's units are finished: its results first, then
             // the count (one thread's fences, as in last_to_arrive)
             drain_writes();
             __syncthreads();
             if (threadIdx.x == 0) {
                 __threadfence();
-                const uint32_t before = mine ? atomicAdd(c + kCtrFinished + pass, mine) : 0u;
-                is_last = mine && before + mine == n_chunks ? 1u : 0u;
-                if (!recount)
-                    while (__hip_atomic_load(c + kCtrFinished + pass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-                           n_chunks)
-                        __builtin_amdgcn_s_sleep(8);
-                __threadfence();
+                is_last = atomicAdd(c + kCtrFinished + pass, mine) + mine == n_units ? 1u : 0u;
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             }
             __syncthreads();
             if (recount && is_last) {
-                // the workgroup that finished the last chunk
+                // the workgroup that finished the last unit
                 if (threadIdx.x == 0) {
                     rows[m].T = s.T;
                     rows[m].I = s.I;

@@ -65,3 +65,36 @@ def test_topk_rows(size, kind):
         compare_step(w, s.host(), ref)
         E_r, W_r = ref["E"], ref["W"]
     s.close()
+
+
+@pytest.mark.parametrize("d", [66_000, 300_003, LONG - 1021])
+def test_rows_that_fall_back_together(d):
+    """One search over rows that fall back and rows that do not, decided by
+    different digits (ties need the index digits, a zero row has no key above
+    the k-th), in units of one to several tiles per wave."""
+    from oracle import oracle as orc
+    kinds = ["gauss", "ties", "zero", "equal", "sparse", "ties", "gauss"]
+    w = custom(d=d, M=len(kinds), kind="topk", k=d // 50, eta=1.0, seed=5)
+    print("case", d, "k", w.k, flush=True)
+    G, E, W = inputs(w)
+    rng = np.random.default_rng(d)
+    for m, kind in enumerate(kinds):
+        x = rng.standard_normal(d, dtype=np.float32)
+        if kind == "ties":
+            x = rng.choice(np.array([0.5, -0.5, 1.0, -0.25], np.float32), size=d)
+        if kind == "zero":
+            x[:] = 0.0
+        if kind == "equal":
+            x[:] = np.where(rng.random(d) < 0.5, np.float32(-2.0), np.float32(2.0))
+        if kind == "sparse":
+            x[rng.random(d) > 0.004] = 0.0
+        G[m, :d] = x
+    E[:] = 0.0
+    s = GpuState(w, G, E, W)
+    E_r, W_r = E.copy(), W.copy()
+    for t in (1, 2):
+        s.fused(t)
+        ref = orc.step(w.as_dict(), np.float32(w.eta), t, G, E_r, W_r)
+        compare_step(w, s.host(), ref)
+        E_r, W_r = ref["E"], ref["W"]
+    s.close()
