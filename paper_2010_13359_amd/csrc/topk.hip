@@ -162,7 +162,10 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *w
 // with runs of 64 none beyond 4.4).  Not single lines: what a run costs is its
 // page's translation (runs of 32 over 16 rows of 10^8: 0.7 TB/s).  Two digits:
 // once error feedback has piled the entries up under the threshold, a 15-bit
-// digit alone (0.8 % of the key's value) holds more than k of them.
+// digit alone (0.8 % of the key's value) holds more than k of them.  Zeros stay
+// out of the histograms, where a sparse row's would all add to one bin (a zero
+// row of 10^6 92 us instead of 12): they lie below all other keys, so a rank
+// that falls among them is just not found, and the band's edge is the lowest.
 constexpr int kSampleRun = 64;  // elements
 constexpr int kSampleThreads = 1024;
 constexpr int kSampleU = 4;  // quads (g and e) in flight per thread
@@ -200,13 +203,17 @@ __device__ __forceinline__ void band_ranks(const SampleArgs &a, uint32_t (&want)
 
 // Finds the bins of both ranks among the counts of a workgroup's threads:
 // thread t holds the bins kSampleBins - 32 (t + 1) .. - 32 t - 1, ascending,
-// in asc.  res[r]: the bin (0xFFFFFFFF: open), res[2 + r]: the rank within it.
+// in asc.  res[r]: the bin (0xFFFFFFFF: open), res[2 + r]: the rank within it (not
+// found, among the zeros: bin 0 and a rank beyond all its counts).
 __device__ __forceinline__ void find_bins(const uint32_t (&asc)[32], const uint32_t (&want)[2], uint32_t *wsum,
                                           uint32_t *res) {
     uint32_t s = 0;
 #pragma unroll
     for (int j = 0; j < 32; ++j) s += asc[j];
-    if (threadIdx.x < 2) res[threadIdx.x] = 0xFFFFFFFFu;
+    if (threadIdx.x < 2) {
+        res[threadIdx.x] = (threadIdx.x == 0 ? want[0] : want[1]) != 0u ? 0u : 0xFFFFFFFFu;
+        res[2 + threadIdx.x] = 0xFFFFFFFFu;
+    }
     uint32_t total;
     const uint32_t excl = block_exclusive_scan(s, wsum, total);  // count above this thread's bins
 #pragma unroll
@@ -240,7 +247,7 @@ __device__ __forceinline__ void write_band(const uint32_t *sub, const uint32_t *
         uint32_t e = wave == 0 ? 0x7FFFFFFFu : 0u;
         if (res[wave] != 0xFFFFFFFFu) {
             uint32_t bin = 0, above = 0;
-            wave_find_desc(sub + wave * kDigitBins, kDigitBins, res[2 + wave], bin, above);
+            wave_find_desc(sub + wave * kDigitBins, kDigitBins, res[2 + wave], bin, above);  // not found: bin 0
             e = (res[wave] << 16) | (bin << 5) | (wave == 0 ? 31u : 0u);
         }
         if ((threadIdx.x & 63) == 0) edge[wave] = e;
@@ -295,7 +302,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_topk_band_row(const float *_
     const int t = threadIdx.x;
     const float *g = G + static_cast<int64_t>(m) * a.ld;
     const float *e = E + static_cast<int64_t>(m) * a.ld;
-    uint32_t key[kRowQuads][4];  // 0xFFFFFFFF: no element
+    uint32_t key[kRowQuads][4];  // 0: no element, or a zero (see above)
 #pragma unroll
     for (int u0 = 0; u0 < kRowQuads; u0 += kSampleU) {
         f32x4 gv[kSampleU], ev[kSampleU];
@@ -317,8 +324,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_topk_band_row(const float *_
             const int64_t i0 = sample_i0(a, n);
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                key[u0 + u][c] = n < a.n_quads && i0 + c < a.d ? key_of(elem(gv[u], c), elem(ev[u], c), a.eta)
-                                                               : 0xFFFFFFFFu;
+                key[u0 + u][c] = n < a.n_quads && i0 + c < a.d ? key_of(elem(gv[u], c), elem(ev[u], c), a.eta) : 0u;
         }
     }
     __syncthreads();
@@ -326,7 +332,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_topk_band_row(const float *_
     for (int u = 0; u < kRowQuads; ++u) {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-            if (key[u][c] != 0xFFFFFFFFu) atomicAdd(&h[bin_at(static_cast<int>(key[u][c] >> 16))], 1u);
+            if (key[u][c] != 0u) atomicAdd(&h[bin_at(static_cast<int>(key[u][c] >> 16))], 1u);
     }
     __syncthreads();
     uint32_t asc[32], want[2];
@@ -341,7 +347,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_topk_band_row(const float *_
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const uint32_t b = key[u][c] >> 16, l = (key[u][c] >> 5) & 0x7FFu;
-            if (key[u][c] == 0xFFFFFFFFu) continue;
+            if (key[u][c] == 0u) continue;
             if (b == res[0]) atomicAdd(&h[l], 1u);
             if (b == res[1]) atomicAdd(&h[kDigitBins + l], 1u);
         }
@@ -381,11 +387,11 @@ __global__ __launch_bounds__(kSampleThreads) void k_topk_sample(const float *__r
         for (int u = 0; u < kSampleU; ++u) {
             const int64_t n = n0 + step * u, i0 = sample_i0(a, n);
             if (n >= a.n_quads) break;
-            uint32_t key[4];  // 0xFFFFFFFF: no element
+            uint32_t key[4];  // 0: no element, or a zero
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                key[c] = i0 + c < a.d ? key_of(elem(gv[u], c), elem(ev[u], c), a.eta) : 0xFFFFFFFFu;
-                if (i0 + c < a.d) atomicAdd(&h[bin_at(static_cast<int>(key[c] >> 16))], 1u);
+                key[c] = i0 + c < a.d ? key_of(elem(gv[u], c), elem(ev[u], c), a.eta) : 0u;
+                if (key[c] != 0u) atomicAdd(&h[bin_at(static_cast<int>(key[c] >> 16))], 1u);
             }
             keys[m * a.n_quads + n] = u32x4{key[0], key[1], key[2], key[3]};
         }
@@ -444,7 +450,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_topk_band(SampleArgs a, cons
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const uint32_t key = elem(kv[u], c), b = key >> 16, l = (key >> 5) & 0x7FFu;
-                if (key == 0xFFFFFFFFu) continue;
+                if (key == 0u) continue;
                 if (b == b0) atomicAdd(&h[l], 1u);
                 if (b == b1) atomicAdd(&h[kDigitBins + l], 1u);
             }
