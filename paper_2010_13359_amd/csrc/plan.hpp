@@ -47,27 +47,64 @@ struct alignas(8) SegConst {
 constexpr double kInfinityCacheBytes = 256.0 * 1024 * 1024;
 
 // The first pass of a step (statistics, top-k counts) reads g and e with
-// ordinary loads where the Infinity Cache holds them, so that the second pass
-// finds them there; the second does so too where the cache also holds what it
+// ordinary loads where the Infinity Cache holds them until the second pass has
+// read them again; the second does so too where the cache also holds what it
 // writes, and the next steps' data.  Otherwise loads stream past the caches
 // (with ordinary loads 32 workers x 2^25, s = 15, take 4790 us instead of
-// 4490).  Whole steps over three states in turn, both passes streaming / the
-// first ordinary / both ordinary, by the size of g and e: 40 MB 33.6 / 33.2 /
-// 28.5 us, 70 MB 48.5 / 47.2 / 44.0, 100 MB 67.1 / 63.5 / 67.4, 140 MB 81.6 /
-// 76.7 / 96.4, 187 MB 112.6 / 103.6 / 132.5, 230 MB 142.4 / 131.3 / 160.0 (4-bit
-// codes; top-k alike); at 262 MB the first line's gain is gone.
-constexpr double kFirstPassCached = 240e6, kBothPassesCached = 85e6;
+// 4490).  What else goes through the cache counts with a weight: w and q-hat,
+// which the second pass reads and writes, and the message planes that it
+// writes by ordinary stores.  By the size of g and e alone, as measured on
+// 4-bit codes of many workers, other steps were up to 17 % slower than with
+// streaming loads.
+//
+// Whole steps over three states in turn: the first pass's ordinary loads stop
+// paying at a g and e of about 50 MB with one worker, 95 with two, 143 with
+// four, 200 with eight, 250 with sixteen, 285 with 32 (signs, 4-bit codes,
+// top-k), and of 117, 145, 178 and 202 MB with 4, 8, 16 and 32 workers, s = 255:
+// within 4 % of g + e + 5 (w + q-hat) + 4 planes = 320 MB.  Below the line
+// both passes streaming / the first ordinary: 16 workers of 140 MB 81.6 / 76.7
+// us, 17 of 187 MB 112.6 / 103.6; above it: 4 workers, s = 255, of 160 MB 97 /
+// 107, 8 of 235 MB 138 / 150.  With eight states in turn (nothing left of the
+// step before) the line lies lower, at three quarters of that with 4 to 16
+// workers; between the two the loss is at most 6 %.
+//
+// Both passes' ordinary loads stop paying at 50 MB with one worker, 58 with
+// two, 72 with four, 83 with eight, 90 with sixteen, 95 with 32, and of the
+// identity, whose plane is as large as e, at about 55: g + e + w + q-hat + 2
+// planes = 100 MB.  The first ordinary / both: 8 workers, signs, of 60 MB
+// 39.0 / 35.9 us; above the line 4 workers, s = 255, of 85 MB 54.5 / 61.0, 8
+// workers, identity, of 82 MB 35.4 / 41.5.
+constexpr double kFirstPassCached = 320e6, kBothPassesCached = 100e6;
 inline double data_bytes(const dqgan_desc &D) { return 8.0 * D.M * static_cast<double>(D.ld); }
-inline bool first_streams(const dqgan_desc &D) { return data_bytes(D) > kFirstPassCached; }
-inline bool second_streams(const dqgan_desc &D) { return data_bytes(D) > kBothPassesCached; }
+inline double vector_bytes(const dqgan_desc &D) { return 8.0 * static_cast<double>(D.ld); }  // w and q-hat
+inline double plane_bytes(const dqgan_desc &D) {  // of those written by ordinary stores
+    const double n = D.M * static_cast<double>(D.ld);
+    switch (D.kind) {
+        case DQGAN_SIGN: return n / 8;
+        case DQGAN_QSGD: return D.levels == 255 ? n * 9 / 8 : n / 8;
+        case DQGAN_MBIT: return D.levels == 8 ? n : 0.0;
+        case DQGAN_IDENTITY: return n * 4;
+        default: return 0.0;
+    }
+}
+inline bool first_streams(const dqgan_desc &D) {
+    return data_bytes(D) + 5 * vector_bytes(D) + 4 * plane_bytes(D) > kFirstPassCached;
+}
+inline bool second_streams(const dqgan_desc &D) {
+    return data_bytes(D) + vector_bytes(D) + 2 * plane_bytes(D) > kBothPassesCached;
+}
 
 // The worker's own calls (encode, update) touch the rows once more each: 20 MB
 // ordinary / streaming 32.5 / 34.0 us for a worker's iteration, 60 MB 67.0 / 65.5,
 // 64 MB 71.9 / 69.3 (s = 255).  The identity has no statistics: its encode is the
-// first pass (120 MB 97.0 / 104.4, 160 MB 133.9 / 138.9).
-constexpr double kWorkerCached = 40e6;
+// first pass and its update the second, with no plane read in between (one
+// worker 120 MB 97.0 / 104.4, 160 MB 133.9 / 138.9, 200 MB 173 / 173, 224 MB 201
+// / 193; two 200 MB 0.93 of streaming, 230 0.97; four 230 MB 0.96; sixteen 230 MB
+// 0.92).
+constexpr double kWorkerCached = 40e6, kWorkerIdentityCached = 275e6;
 inline bool worker_streams(const dqgan_desc &D) {
-    return D.kind == DQGAN_IDENTITY ? first_streams(D) : data_bytes(D) > kWorkerCached;
+    return D.kind == DQGAN_IDENTITY ? data_bytes(D) + vector_bytes(D) / 2 > kWorkerIdentityCached
+                                    : data_bytes(D) > kWorkerCached;
 }
 
 // f(STREAM) with `streams` as a compile-time constant.
