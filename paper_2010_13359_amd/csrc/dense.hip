@@ -1272,7 +1272,9 @@ hipError_t fused_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
 // Cache holds, and plans of short segments, whose waves wait for look-ups and
 // constants rather than for HBM (apply pass with the cap / without: 32 workers
 // x 4M, s = 15, segments of 150 550 / 487 us, 601 502 / 452, 2401 470 / 434,
-// 5001 and more within 1 %; 16 workers, signs, 150 229 / 209, 601 205 / 209).
+// 5001 and more within 1 %; 16 workers, signs, 150 229 / 209, 601 205 / 209),
+// and top-k with four rows per wave (whole step 17 workers of 4 GB 0.944 of the
+// capped, 28 0.937, 32 0.974; with two rows per wave, 16 workers, 1.028).
 constexpr int kLdsPerCu = 160 * 1024;
 constexpr int64_t kShortSegment = 4096;  // mean elements below which a plan's segments are short
 unsigned cap_lds(int R, int NG, int waves) {
@@ -1294,7 +1296,8 @@ hipError_t split_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G,
     // HBM (see cap_lds).
     const double bytes = 16.0 * P.desc.M * static_cast<double>(P.desc.ld);
     const bool short_segs = KIND != kTopk && KIND != kIdentity && P.desc.d < kShortSegment * P.desc.n_seg;
-    const unsigned cap = bytes > kInfinityCacheBytes && !short_segs ? cap_lds(R, NG, static_cast<int>(block.x / 64)) : 0u;
+    const bool capped = bytes > kInfinityCacheBytes && !short_segs && !(KIND == kTopk && R == 4);
+    const unsigned cap = capped ? cap_lds(R, NG, static_cast<int>(block.x / 64)) : 0u;
     auto go = [&](auto io) {
         hipLaunchKernelGGL((k_fused_split<KIND, LB, R, NG, NB, decltype(io)::value>), grid, block, cap, st, G, E, W, WX,
                            Qhat, w.sign, w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a, inv_m(P.desc.M), ta);
