@@ -539,9 +539,9 @@ __global__ __launch_bounds__(kBlock) void k_encode_rows(const float *__restrict_
     }
 }
 
-// The fused step.  MT > 0: M == MT, the extrapolation operands stay in
-// registers; MT == 0: any M, the second sweep re-reads g and the new e.
-template <int KIND, int LB, int MT>
+// The fused step, any M: one lane walks all rows; the second sweep re-reads g
+// and the new e.
+template <int KIND, int LB>
 __global__ __launch_bounds__(kBlock) void k_fused(const float *__restrict__ G, float *__restrict__ E,
                                                   float *__restrict__ W, float *__restrict__ WX,
                                                   float *__restrict__ Qhat, uint32_t *__restrict__ sign_plane,
@@ -553,13 +553,11 @@ __global__ __launch_bounds__(kBlock) void k_fused(const float *__restrict__ G, f
     const int64_t i0 = 4 * q;
     // top-k: each wave's 64 quads are one counting tile
     const int64_t tile = static_cast<int64_t>(blockIdx.x) * (kQuadsPerBlock / 64) + (threadIdx.x >> 6);
-    const int M = MT > 0 ? MT : a.M;
-    constexpr int kUnroll = MT > 0 ? MT : 1;
+    const int M = a.M;
     int js[4];
     lookup_segments(off, tile_seg, i0, a.d, js);
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4 xs[MT > 0 ? MT : 1];
-#pragma unroll kUnroll
+#pragma unroll 1
     for (int m = 0; m < M; ++m) {
         const int64_t rb = static_cast<int64_t>(m) * a.ld;
         const f32x4 g = ld_stream(G + rb + i0);
@@ -585,12 +583,6 @@ __global__ __launch_bounds__(kBlock) void k_fused(const float *__restrict__ G, f
 #pragma unroll
             for (int c = 0; c < 4; ++c) set_elem(acc, c, add_rn(elem(acc, c), elem(cq.phat, c)));
         }
-        if (MT > 0) {
-            f32x4 x;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) set_elem(x, c, add_rn(elem(cq.eg, c), elem(cq.enew, c)));
-            xs[MT > 0 ? m : 0] = x;
-        }
     }
     f32x4 qh;
 #pragma unroll
@@ -606,18 +598,14 @@ __global__ __launch_bounds__(kBlock) void k_fused(const float *__restrict__ G, f
     for (int c = 0; c < 4; ++c) set_elem(wt, c, sub_rn(elem(w, c), elem(qh, c)));
     st4(W + i0, wt);
     if (Qhat) st4(Qhat + i0, qh);
-#pragma unroll kUnroll
+#pragma unroll 1
     for (int m = 0; m < M; ++m) {
         const int64_t rb = static_cast<int64_t>(m) * a.ld;
+        const f32x4 g = ld4(G + rb + i0);
+        const f32x4 en = ld4(E + rb + i0);
         f32x4 x;
-        if (MT > 0) {
-            x = xs[MT > 0 ? m : 0];
-        } else {
-            const f32x4 g = ld4(G + rb + i0);
-            const f32x4 en = ld4(E + rb + i0);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) set_elem(x, c, add_rn(mul_rn(a.eta, elem(g, c)), elem(en, c)));
-        }
+        for (int c = 0; c < 4; ++c) set_elem(x, c, add_rn(mul_rn(a.eta, elem(g, c)), elem(en, c)));
         f32x4 wx;
 #pragma unroll
         for (int c = 0; c < 4; ++c) set_elem(wx, c, (i0 + c < a.d) ? sub_rn(elem(wt, c), elem(x, c)) : 0.0f);
@@ -1251,10 +1239,10 @@ TopkArgs topk_args(const dqgan_plan_s &P, const dqgan_wire &w) {
     return ta;
 }
 
-template <int KIND, int LB, int MT>
+template <int KIND, int LB>
 hipError_t fused_launch(const dqgan_plan_s &P, const RowArgs &a, const float *G, float *E, float *W, float *WX,
                         const dqgan_wire &w, float *Qhat, hipStream_t st) {
-    hipLaunchKernelGGL((k_fused<KIND, LB, MT>), dim3(static_cast<unsigned>(P.n_tiles)), dim3(kBlock), 0, st, G, E, W,
+    hipLaunchKernelGGL((k_fused<KIND, LB>), dim3(static_cast<unsigned>(P.n_tiles)), dim3(kBlock), 0, st, G, E, W,
                        WX, Qhat, w.sign, w.level, w.val, P.d_consts, P.d_off, P.d_tile_seg, a, inv_m(P.desc.M),
                        topk_args(P, w));
     return hipGetLastError();
@@ -1334,7 +1322,7 @@ hipError_t fused_by_m(const dqgan_plan_s &P, const RowArgs &a, const float *G, f
     if (M <= 64) return split_launch<KIND, LB, 4, 16>(P, a, G, E, W, WX, w, Qhat, st);
     if (M <= 128) return split_launch<KIND, LB, 8, 16>(P, a, G, E, W, WX, w, Qhat, st);
     if (M <= 256) return split_launch<KIND, LB, 4, 16, 4>(P, a, G, E, W, WX, w, Qhat, st);
-    return fused_launch<KIND, LB, 0>(P, a, G, E, W, WX, w, Qhat, st);
+    return fused_launch<KIND, LB>(P, a, G, E, W, WX, w, Qhat, st);
 }
 
 }  // namespace

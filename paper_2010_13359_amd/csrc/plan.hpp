@@ -126,12 +126,9 @@ struct TopkRow {
     uint32_t fallback;   // 1: the band missed the k-th key; the full-row search decides
     uint32_t T, I;       // the selection
     uint32_t n_spill;    // candidates a wave could not stage: stored from the top of the row's list down
-    uint32_t slots;      // bit p: the candidate search built digit histogram p in this iteration
-    uint32_t pad1;
-    uint32_t pad0;
     uint32_t total;      // selected count found by the tile scan (equals k)
     uint32_t n_above;    // keys above the band, counted by the full pass
-    uint32_t pad[4];
+    uint32_t pad[7];
 };
 
 constexpr int kTopkTile = 256;            // elements per counting tile (one wave of quads)

@@ -6,7 +6,9 @@
 // (key, ~index): element i is selected iff key > T, or key == T and i <= I.
 //
 // Per row, with one full read of g and e:
-//  1. sample: one 256-element chunk per 65536 elements, histogram of key>>16;
+//  1. sample: runs of 64 elements, 512 of them in a row that one workgroup
+//     searches, 4096 in a longer one; histograms of key >> 16 and, within the
+//     bins that hold the band's ends, of the next 11 bits;
 //  2. band: the sample ranks k/d * s -+ 8 sigma bracket the k-th key in a
 //     band [lo, hi];
 //  3. full pass: per 256-element tile the number of keys above hi; every
@@ -293,7 +295,6 @@ constexpr int kRowQuads = 8;  // quads per thread
 
 __global__ __launch_bounds__(kSampleThreads) void k_topk_band_row(const float *__restrict__ G,
                                                                   const float *__restrict__ E, SampleArgs a,
-                                                                  uint32_t *__restrict__ sel_hist,
                                                                   TopkRow *__restrict__ rows,
                                                                   uint32_t *__restrict__ ctr) {
     __shared__ uint32_t h[kSampleBins];
@@ -316,7 +317,6 @@ __global__ __launch_bounds__(kSampleThreads) void k_topk_band_row(const float *_
         if (u0 == 0) {
             for (int b = t; b < kSampleBins / 4; b += kSampleThreads)
                 reinterpret_cast<u32x4 *>(h)[b] = u32x4{0u, 0u, 0u, 0u};
-            for (int b = t; b < kDigitBins; b += kSampleThreads) sel_hist[static_cast<int64_t>(m) * kDigitBins + b] = 0u;
         }
 #pragma unroll
         for (int u = 0; u < kSampleU; ++u) {
@@ -579,7 +579,8 @@ __global__ __launch_bounds__(kBlock) void k_topk_pass(const float *__restrict__ 
                     ns += tot;
                 } else {
                     // the wave's staging is full: these go to the top of the
-                    // row's list, counted per tile by k_topk_spill_count
+                    // row's list, counted per tile by the search (short rows)
+                    // or by k_topk_fallback
                     uint32_t sbase = 0;
                     if (lane == 0) sbase = atomicAdd(ctr + static_cast<int64_t>(m) * kRowCtrWords + kCtrSpill, tot);
                     sbase = __builtin_amdgcn_readfirstlane(sbase);
@@ -2006,18 +2007,19 @@ hipError_t topk_alloc(dqgan_plan_s &P) {
         S.coarse = S.ref_hist + M * 2 * kDigitBins;
         S.done = S.coarse + M * 4;
     }
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&S.sel_hist), M * kDigitBins * sizeof(uint32_t));
+    if (e == hipSuccess && !S.row_search)
+        e = hipMalloc(reinterpret_cast<void **>(&S.sel_hist), M * kDigitBins * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&S.fb_hist), digit_words * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&S.cand), M * static_cast<size_t>(S.cap) * sizeof(uint2));
     if (e == hipSuccess)
         e = hipMalloc(reinterpret_cast<void **>(&S.play), M * static_cast<size_t>(S.cap) * sizeof(uint2));
-    if (e == hipSuccess)
+    if (e == hipSuccess && !S.row_search)
         e = hipMalloc(reinterpret_cast<void **>(&S.runs), M * static_cast<size_t>(S.n_chunks) * sizeof(uint2));
     if (e == hipSuccess)
         e = hipMalloc(reinterpret_cast<void **>(&S.tile_cnt), M * static_cast<size_t>(S.n_tiles) * sizeof(uint16_t));
     if (e == hipSuccess)
         e = hipMalloc(reinterpret_cast<void **>(&S.tile_off), M * static_cast<size_t>(S.n_tiles) * sizeof(uint16_t));
-    if (e == hipSuccess)
+    if (e == hipSuccess && !S.row_search)
         e = hipMalloc(reinterpret_cast<void **>(&S.chunk_sum), M * static_cast<size_t>(S.n_chunks) * sizeof(uint32_t));
     if (e == hipSuccess)
         e = hipMalloc(reinterpret_cast<void **>(&S.chunk_off), M * static_cast<size_t>(S.n_chunks) * sizeof(uint32_t));
@@ -2057,7 +2059,7 @@ hipError_t launch_topk_select(const dqgan_plan_s &P, float eta, const float *G, 
     uint32_t *cidx = ckey + static_cast<int64_t>(D.M) * S.cap;
     const SampleArgs sa{eta, D.d, D.ld, D.k, S.n_sample_quads, S.sample_stride, S.n_samples};
     if (S.row_search) {
-        hipLaunchKernelGGL(k_topk_band_row, dim3(M), dim3(kSampleThreads), 0, st, G, E, sa, S.sel_hist, S.rows, S.ctr);
+        hipLaunchKernelGGL(k_topk_band_row, dim3(M), dim3(kSampleThreads), 0, st, G, E, sa, S.rows, S.ctr);
     } else {
         // one workgroup per CU; each takes at least kSampleU quads per thread
         const int64_t most = (S.n_sample_quads + kSampleThreads * kSampleU - 1) / (kSampleThreads * kSampleU);
