@@ -1,6 +1,6 @@
 """Seeded random shapes through the C ABI against the oracle (teacher-forced,
-bit-exact): every compressor, worker counts 1..140 (every launch shape of the fused
-kernel), lengths 1..60000 with ragged tails, random segment layouts down to
+bit-exact): every compressor, worker counts 1..140 (the launch shapes of the fused
+kernel that keep a worker's row in one wave), lengths 1..60000 with ragged tails, random segment layouts down to
 one-element segments, random step sizes and residual magnitudes."""
 import numpy as np
 import pytest

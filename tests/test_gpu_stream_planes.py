@@ -8,10 +8,12 @@ sign-magnitude codes.
 The iteration is checked against the oracle, teacher-forced with the GPU's
 segment scales, on windows at the start of the row, across a segment
 boundary, in the middle and at the ragged end; the scales of the sampled
-segments against the oracle's own within 1e-5.  Also with M = 130 (the
-one-lane kernel), and for the worker side alone (dqgan_compress_ef) and
-dqgan_pack, which choose the store kind at run time.  Inputs are drawn on
-the device; only windows are copied to the host.
+segments against the oracle's own within 1e-5.  Also with M = 130 (rows in
+blocks of 64) and M = 257 (the one-lane kernel, which chooses the store kind at
+run time), and for the worker side alone (dqgan_compress_ef) and dqgan_pack,
+which choose it too.  Then smaller planes with streamed loads: 256 workers in
+blocks, and the worker side's form for fewer than four rows.  Inputs are drawn
+on the device; only windows are copied to the host.
 """
 import numpy as np
 import pytest
@@ -157,15 +159,16 @@ def test_streamed_plane_windows(case):
 
 
 @pytest.mark.timeout(600)
-@pytest.mark.parametrize("kind,levels,d", [("qsgd", 255, 2_300_001), ("mbit", 4, 4_500_003)])
-def test_streamed_plane_many_workers(kind, levels, d):
-    """M = 130: the one-lane-per-quad fused kernel, which picks the store kind
-    at run time."""
+@pytest.mark.parametrize("kind,levels,d,M", [("qsgd", 255, 2_300_001, 130), ("mbit", 4, 4_500_003, 130),
+                                             ("qsgd", 255, 1_200_001, 257), ("mbit", 4, 2_200_003, 257)])
+def test_streamed_plane_many_workers(kind, levels, d, M):
+    """M = 130: rows in blocks of 64 by the split kernel.  M = 257: the
+    one-lane-per-quad kernel, which picks the store kind at run time."""
     import torch
     from paper_2010_13359_amd import dqgan
-    w = custom(d=d, M=130, kind=kind, levels=levels, norm="l2", seg_offsets=[0, 1_000_001, d], eta=1e-3, seed=43)
+    w = custom(d=d, M=M, kind=kind, levels=levels, norm="l2", seg_offsets=[0, 1_000_001, d], eta=1e-3, seed=43)
     assert _plane_bytes(w) > 256 * 2 ** 20
-    print("streamed plane, M = 130: %s %d d=%d" % (kind, levels, d), flush=True)
+    print("streamed plane, M = %d: %s %d d=%d" % (M, kind, levels, d), flush=True)
     G, E, W = _device_state(w, 43)
     E0, W0 = E.clone(), W.clone()
     plan = dqgan.Plan.from_workload(w)
@@ -174,7 +177,7 @@ def test_streamed_plane_many_workers(kind, levels, d):
     t = 2
     dqgan.step_fused(plan, w.eta, t, G, E, W, WX, wire)
     torch.cuda.synchronize()
-    _check_windows(w, t, G, E0, W0, E, W, WX, wire, rows=(0, 1, 64, 65, 128, 129))
+    _check_windows(w, t, G, E0, W0, E, W, WX, wire, rows=(0, 1, 64, 65, 128, 129, M - 1))
     plan.close()
 
 
@@ -232,4 +235,42 @@ def test_streamed_plane_worker_side_and_pack(kind, levels):
                 got_l = _words(packed.level.view(w.M, -1)[m], a, b, lbits)
                 assert_same("packed signs [%d,%d) row %d" % (a, b, m), got_s, exp_s[:len(got_s)])
                 assert_same("packed levels [%d,%d) row %d" % (a, b, m), got_l, exp_l[:len(got_l)])
+    plan.close()
+
+
+# more than 100 MB of g and e (the fused pass streams its loads) in planes that
+# the caches take, and more than 40 MB in tiles that are no multiple of four
+# (the worker's calls stream theirs) with the last one ragged
+LOADS = [("qsgd", 255, "l2", 60_001, 256), ("mbit", 4, "l2", 70_003, 193), ("sign", 0, "l1", 60_001, 256),
+         ("qsgd", 255, "l2", 6_001_123, 1), ("mbit", 4, "linf", 2_001_123, 3), ("sign", 0, "l1", 3_001_123, 2)]
+
+
+@pytest.mark.parametrize("kind,levels,norm,d,M", LOADS)
+def test_streamed_loads(kind, levels, norm, d, M):
+    """The fused step on windows against the oracle, and the separate worker
+    and server calls against the fused step bit for bit."""
+    import torch
+    from paper_2010_13359_amd import dqgan
+    offs = [0, 33_333, d - 20_001, d]
+    w = custom(d=d, M=M, kind=kind, levels=levels, norm=norm, seg_offsets=offs, eta=1e-3, seed=53)
+    print("streamed loads: %s %d M=%d d=%d" % (kind, levels, M, d), flush=True)
+    G, E, W = _device_state(w, 53)
+    E0, W0 = E.clone(), W.clone()
+    plan = dqgan.Plan.from_workload(w)
+    WX, Q = torch.empty_like(G), torch.empty_like(W)
+    fused, apart = plan.new_wire(G.device), plan.new_wire(G.device)
+    dqgan.step_fused(plan, w.eta, 5, G, E, W, WX, fused, Q)
+    E1, W1, WX1, Q1 = E0.clone(), W0.clone(), torch.empty_like(G), torch.empty_like(W)
+    dqgan.compress_ef(plan, w.eta, 5, G, E1, None, apart)
+    dqgan.aggregate(plan, apart, Q1)
+    dqgan.omd_step(plan, w.eta, Q1, W1, G, E1, WX1)
+    torch.cuda.synchronize()
+    for name in ("sign", "level", "scale"):
+        a, b = getattr(fused, name), getattr(apart, name)
+        if a is not None:
+            assert torch.equal(a, b), name
+    for name, a, b in (("e", E, E1), ("w", W, W1), ("wx", WX, WX1), ("qhat", Q, Q1)):
+        assert torch.equal(a, b), name
+    if kind != "sign":
+        _check_windows(w, 5, G, E0, W0, E, W, WX, fused, rows=sorted({0, M // 2, M - 1}))
     plan.close()
