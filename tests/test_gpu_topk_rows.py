@@ -2,8 +2,9 @@
 row stops searching alone (8192 tiles of 256), over key distributions that
 take each branch: a Gaussian row, entries piled up in a narrow range of keys
 (the second digit of the band, many candidates in one bin), heavy ties and
-zero rows (the full-row search, with and without its index digits), a large
-cluster that no sampled run meets, and a dense band that overflows a wave's
+zero rows (the full-row search, with and without its index digits), more than
+k large entries that no sampled run meets (the keys above the band are k or
+more: the search hands the row over), and a dense band that overflows a wave's
 staging.  Two iterations, so that the histograms and counters that must be
 zero between iterations are; everything against the oracle."""
 import numpy as np
@@ -20,6 +21,28 @@ SIZES = {"d511": 511, "d513": 513, "d66000": 66000, "short_edge": SHORT - 3, "lo
 KINDS = ["gauss", "piled", "ties", "zeros", "cluster", "band", "equal"]
 
 
+RUN = 64  # elements of a sampled run
+
+
+def _sample_stride(w):
+    """Elements from one sampled run of a row to the next: 512 runs at most in
+    the short rows, 4096 in longer ones."""
+    short = w.ld // 256 <= 8192
+    most = 512 if short else 4096
+    return max(512 if short else 2048, (-(-w.d // most) + RUN - 1) // RUN * RUN)
+
+
+def _band_misses(w, x):
+    """Whether k or more keys of a row lie above the band that its sample gives."""
+    at = np.arange(w.d) % _sample_stride(w) < RUN
+    ns, f = int(at.sum()), w.k / w.d
+    upper = int(np.floor(f * ns - 8.0 * (np.sqrt(ns * f * (1.0 - f)) + 1.0)))  # + 1: the rank of the upper end
+    if upper < 1:
+        return False  # the band is open
+    hi = np.sort(np.abs(x[at]))[::-1][upper]
+    return int((np.abs(x) > hi * np.float32(1.0 + 2.0 ** -17)).sum()) >= w.k
+
+
 def _gradients(kind, w):
     rng = np.random.default_rng(len(kind) + w.d % 1000)
     n = (w.M, w.d)
@@ -33,9 +56,9 @@ def _gradients(kind, w):
         x[0] = 0.0
         x[1, :: 7] = 0.0
         x[1, w.k // 2:] = 0.0    # fewer than k entries that are not zero
-    if kind == "cluster":        # more than k large entries between two sampled runs
-        a = min(100, w.d // 3)
-        x[:, a:a + min(w.d // 4, 300)] *= 1000.0
+    if kind == "cluster":        # more than k large entries, all between the sampled runs
+        away = np.flatnonzero(np.arange(w.d) % _sample_stride(w) >= RUN)
+        x[:, rng.choice(away, min(len(away), w.k + w.k // 4 + 1), replace=False)] *= 1000.0
     if kind == "band":           # a run of entries just around the k-th largest
         a, b = w.d // 4, w.d // 4 + max(1, w.k // 2)
         x *= 1e-3
@@ -57,6 +80,8 @@ def test_topk_rows(size, kind):
     G, E, W = inputs(w)
     G[:, :d] = _gradients(kind, w)
     E[:] = 0.0
+    if kind == "cluster" and d > 1000:  # (the shortest rows' bands are open)
+        assert all(_band_misses(w, G[m, :d]) for m in range(w.M))
     s = GpuState(w, G, E, W)
     E_r, W_r = E.copy(), W.copy()
     for t in (1, 2):
