@@ -235,9 +235,10 @@ dqgan_status dqgan_step_apply(dqgan_plan plan, float eta, uint32_t t, const floa
  *   (held until the process ends).  They need about
  *   12 M P + 16 P + 8 M S + ld/256 + 12 S bytes (P = number of pieces,
  *   sum over segments of ceil(n_j / piece), piece = 32768 elements when
- *   M * floor(d / 32768) >= 16384, else 16384; S = n_seg; every table
- *   rounded up to 256 bytes); a workload above 8 MiB, or with more than 255
- *   segments, returns DQGAN_ESCRATCH and enqueues nothing.
+ *   M * floor(d / 32768) >= 16384, else 16384 when M * floor(d / 16384) >=
+ *   2048, else 16380; S = n_seg; every table rounded up to 256 bytes); a
+ *   workload above 8 MiB, or with more than 255 segments, returns
+ *   DQGAN_ESCRATCH and enqueues nothing.
  *   The array is shared by every call on the device and keeps the last
  *   call's contents (every table is rewritten at each call, nothing relies
  *   on earlier contents): calls that overlap on one device race.
